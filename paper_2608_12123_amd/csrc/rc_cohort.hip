@@ -4,9 +4,13 @@
 // Kernels
 //   rc_prep_kernel    once per handle: builds the route-table image that every
 //                     workgroup stages into LDS.
-//   rc_chain_kernel   device-resident chain (Section 7 "Device resident"):
-//                     one launch runs T chained steps; state lives in VGPRs,
-//                     decisions never leave the chip.
+//   rc_lanes_kernel   once per handle (table image): what every plan lane
+//                     needs to know of its session and cohort.
+//   rc_chain_kernel, rc_table_kernel
+//                     device-resident chain (Section 7 "Device resident"),
+//                     with the full or the table image: one launch runs T
+//                     chained steps; state lives in VGPRs, decisions never
+//                     leave the chip.
 //   rc_decide_kernel  host-round-trip step, part 1 (Section 7 "Host round
 //                     trip"): decide + compact, publish a 4-byte word.
 //   rc_body_kernel    host-round-trip step, part 2: one route body over the
@@ -23,13 +27,13 @@
 // workgroup barrier -- each into the first wavefront of the open bin with room
 // for it, so a wavefront can hold several cohorts that are not neighbours --
 // and larger cohorts go, in order, into "multi-wavefront" bins.  A bin is one
-// workgroup of 4 or 8 wavefronts.  A cohort of at most 64 sessions never
+// workgroup of 4 wavefronts of plan lanes.  A cohort of at most 64 sessions never
 // straddles a wavefront; a larger one starts on a wavefront boundary and spans
 // whole wavefronts; no cohort straddles a bin.  Each wavefront has a 64-byte
 // descriptor read with scalar loads.  The compaction
 // (stable partition, taken first) is a wavefront ballot + mbcnt rank; a
 // cohort spanning wavefronts adds an LDS exchange of per-wavefront popcounts
-// behind one workgroup barrier per step.
+// behind one workgroup barrier per chunk of steps.
 //
 // Route-table image in LDS.
 //   full:  row r < R holds the W masks table[r][w mod 16] * (w + 1); row R is
@@ -38,26 +42,19 @@
 //          row R is zero; the masks are formed in registers with full-rate
 //          shifts and adds: the mask of w + 16 is the mask of w plus
 //          table[r][w mod 16] << 4 (exact modulo 2^32).
-// Block q (16 bytes) of row r is stored at block q ^ (r mod blocks-per-row)
-// to spread lanes reading different rows over the LDS banks.  After the rows
-// come the tool pairs (full image), the route thresholds and, in CDF mode, a
-// guide table: guide[b] is the route of outcome b * 2^(32-g), so the route
-// of o lies in [guide[o >> (32-g)], guide[(o >> (32-g)) + 1]] and a short
-// binary search of fixed trip count finishes it (the indexed-search guide
-// table of Chen and Asau, 1974).
+// Ahead of the rows comes what the word-0 chain reads: word 0's masks (table
+// image: with the tools and the rows' addresses), the route thresholds and,
+// in CDF mode, a guide table: guide[b] is the route of outcome b * 2^(32-g),
+// so the route of o lies in [guide[o >> (32-g)], guide[(o >> (32-g)) + 1]]
+// (the indexed-search guide table of Chen and Asau, 1974); a binary search
+// narrows it to three thresholds where a bucket holds more, and those are
+// read together and counted.
 //
 // Per-word update, branch-free.  With d the decision and r the route:
 //   sh = d ? 0 : (31 - r) mod 32      rotl by (r+1) mod 32 == rotr by sh
 //   M  = masks of row (d ? r : R)      (zero when not taken)
 //   oo = d ? 0 : o
 //   S' = (rotr(S, sh) ^ M) + oo       one v_alignbit_b32 + one v_xad_u32
-//
-// Step schedule.  The decision of step t + 1 needs only word 0 after step
-// t, so it is made right after words 0..3 are updated; its popcount is
-// published and the workgroup barrier is passed there, the next mask row is
-// prefetched, and only then are the remaining words updated -- so the
-// barrier, the count exchange and the LDS latency overlap the bulk update.
-// The effects of step t are stored at the end of step t.
 
 #include <hip/hip_runtime.h>
 
@@ -143,13 +140,6 @@ __device__ __forceinline__ uint32_t opaque_s(uint32_t v) {
     return v;
 }
 
-// `m` with a false data dependence on `after`: m cannot be formed before
-// `after` is.  Used to keep one band of masks live at a time.
-__device__ __forceinline__ uint32_t after_word(uint32_t m, uint32_t after) {
-    asm("" : "+v"(m) : "v"(after));
-    return m;
-}
-
 __device__ __forceinline__ uint32_t lane_rank(uint64_t m) {
     // number of set bits of m below this lane
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
@@ -183,10 +173,23 @@ __device__ __forceinline__ void st128(uint32_t* base, uint32_t byte_off, uint4 v
     else *p = x;
 }
 
+// A row base held in scalar registers, in the global address space (an opaque
+// generic pointer would make the access a flat one).
+typedef __attribute__((address_space(1))) uint32_t* gptr;
+__device__ __forceinline__ uint32_t ldg(gptr base, uint32_t byte_off) {
+    typedef const __attribute__((address_space(1))) char* bytes;
+    return *reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(reinterpret_cast<bytes>(base) + byte_off);
+}
+__device__ __forceinline__ void stg_nt(gptr base, uint32_t byte_off, uint32_t v) {
+    typedef __attribute__((address_space(1))) char* bytes;
+    __builtin_nontemporal_store(v, reinterpret_cast<gptr>(reinterpret_cast<bytes>(base) + byte_off));
+}
+
 struct RouteArgs {
     uint32_t mode;        // RC_ROUTE_MOD / RC_ROUTE_CDF
     uint32_t n_routes;    // R
     uint32_t pow2_mask;   // R - 1 when R is a power of two, else 0
+    uint32_t mod_recip;   // floor(2^32 / R) when R is not
     uint32_t is_pow2;
     uint32_t cdf_n;       // R - 1 thresholds
     uint32_t cdf_top;     // largest power of two <= cdf_n (0 if none)
@@ -194,8 +197,21 @@ struct RouteArgs {
     uint32_t guide_top;   // largest step of the search inside a guide bucket
 };
 
+// o mod R by the reciprocal m = floor(2^32 / R): o m / 2^32 is below o / R by
+// less than o / 2^32 < 1, so its floor is the quotient or one less, and one
+// conditional subtraction finishes it (a general 32-bit remainder is about
+// four times the instructions, on the serial path of the chain).
+__device__ __forceinline__ uint32_t mod_routes(uint32_t o, const RouteArgs& ra) {
+    const uint32_t x = o - __umulhi(o, ra.mod_recip) * ra.n_routes;  // < 2 R
+    const uint32_t y = x - ra.n_routes;
+    return x < y ? x : y;  // y wraps above x when x < R
+}
+
 // Route kinds, fixed per kernel instantiation.
 enum : int { RK_POW2 = 0, RK_MOD = 1, RK_CDF = 2 };
+
+// Words of padding (2^32 - 1) behind the thresholds in LDS.
+constexpr uint32_t CDF_PAD = 3;
 
 // Route key: o mod R, or (CDF) from the LDS thresholds and guide table (see
 // the file comment), with a branch-free search of fixed trip count.
@@ -205,20 +221,32 @@ __device__ __forceinline__ uint32_t route_of(uint32_t o, const RouteArgs& ra,
     if constexpr (RK == RK_POW2) {
         return o & ra.pow2_mask;
     } else if constexpr (RK == RK_MOD) {
-        return o % ra.n_routes;
+        return mod_routes(o, ra);
     } else {
         const uint32_t bkt = o >> ra.guide_shift;
         uint32_t pos = guide[bkt];
-        const uint32_t hi = guide[bkt + 1u];
-        for (uint32_t stp = ra.guide_top; stp != 0u; stp >>= 1) {
-            const uint32_t i = pos + stp;
-            const uint32_t j = i < hi ? i : hi;          // min(i, hi)
-            const uint32_t v = cdf[(j > 1u ? j : 1u) - 1u];  // always in range
-            // both tests evaluated (no short circuit), so the read needs no
-            // branch around it
-            pos = ((i <= hi) & (v <= o)) ? i : pos;
+        if (ra.guide_top > 2u) {  // more than three thresholds in some bucket
+            const uint32_t hi = guide[bkt + 1u];
+            for (uint32_t stp = ra.guide_top; stp > 2u; stp >>= 1) {
+                const uint32_t i = pos + stp;
+                const uint32_t j = i < hi ? i : hi;              // min(i, hi)
+                const uint32_t v = cdf[(j > 1u ? j : 1u) - 1u];  // always in range
+                // both tests evaluated (no short circuit), so the read needs
+                // no branch around it
+                pos = ((i <= hi) & (v <= o)) ? i : pos;
+            }
         }
-        return pos;
+        // At most three thresholds are left (one, where no bucket holds more):
+        // read together, one LDS latency, and counted.  Those past the answer
+        // are above o; the padding behind the last one counts only for
+        // o = 2^32 - 1, whose route is R - 1.
+        uint32_t below = cdf[pos] <= o;
+        if (ra.guide_top > 1u) {
+            const uint32_t v1 = cdf[pos + 1u], v2 = cdf[pos + 2u];
+            below += (uint32_t)(v1 <= o) + (uint32_t)(v2 <= o);
+        }
+        pos += below;
+        return pos < ra.cdf_n ? pos : ra.cdf_n;
     }
 }
 
@@ -227,7 +255,7 @@ __device__ __forceinline__ uint32_t route_of(uint32_t o, const RouteArgs& ra,
 __device__ __forceinline__ uint32_t route_of_bsearch(uint32_t o, const RouteArgs& ra,
                                                      const uint32_t* cdf) {
     if (ra.mode == RC_ROUTE_MOD)
-        return ra.is_pow2 ? (o & ra.pow2_mask) : (o % ra.n_routes);
+        return ra.is_pow2 ? (o & ra.pow2_mask) : mod_routes(o, ra);
     uint32_t pos = 0;
     for (uint32_t stp = ra.cdf_top; stp != 0u; stp >>= 1) {
         const uint32_t i = pos + stp;
@@ -308,10 +336,6 @@ __device__ __forceinline__ void publish_count(const LaneCohort& L, uint64_t bal,
         cnt_lds[(pub & 1u) * cnt_stride + wv] = (uint32_t)__popcll(bal);
 }
 
-// DEFER: the values are left in VGPRs and made uniform only when the slot is
-// computed, so the LDS latency overlaps other work; otherwise they move to
-// SGPRs at once (for kernels short of VGPRs).
-template <bool DEFER = false>
 __device__ __forceinline__ void barrier_read_counts(const LaneCohort& L, const uint32_t* cnt_lds,
                                                     uint32_t cnt_stride, uint32_t& pub,
                                                     uint32_t (&c4)[4]) {
@@ -319,7 +343,7 @@ __device__ __forceinline__ void barrier_read_counts(const LaneCohort& L, const u
     if (L.flags & WF_MULTI) {
         const uint32_t* buf = cnt_lds + (pub & 1u) * cnt_stride + (L.flags >> 24);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) c4[i] = DEFER ? buf[i] : uni(buf[i]);
+        for (int i = 0; i < 4; ++i) c4[i] = uni(buf[i]);
     }
     pub += 1u;
 }
@@ -367,7 +391,7 @@ struct ImageArgs {
     uint32_t* max_span;   // out: largest guide bucket span
     uint32_t n_routes, row_words, full, tab_words, tools_off, cdf_off, cdf_n;
     uint32_t guide_off, guide_n, guide_shift, total_words;
-    uint32_t m0_words, rows_off;  // full image: word-0 masks at 0, rows at rows_off
+    uint32_t m0_words, rows_off;  // word-0 masks (full) or route pairs (table) at 0, rows at rows_off
 };
 
 // number of thresholds <= x (plain binary search over global memory)
@@ -380,6 +404,15 @@ __device__ __forceinline__ uint32_t count_le(const uint32_t* cdf, uint32_t n, ui
     return lo;
 }
 
+// Table image: where row r's block 0 lies, in 16-byte units of LDS, as the
+// high half of a control word.  Block q of row r is stored at block
+// q ^ (r / 4 mod 4) of its 64 bytes (rows_off is a multiple of 16 words), so
+// that lanes reading one block of random rows spread over all 16 bank groups
+// (64-byte rows alone reach four) and every block is one XOR away.
+__host__ __device__ __forceinline__ uint32_t table_row_field(uint32_t rows_off, uint32_t r) {
+    return (rows_off / 4u + r * 4u + ((r >> 2) & 3u)) << 16;
+}
+
 __global__ __launch_bounds__(256) void rc_prep_kernel(ImageArgs a) {
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     if (i >= a.total_words) return;
@@ -388,6 +421,11 @@ __global__ __launch_bounds__(256) void rc_prep_kernel(ImageArgs a) {
     if (a.full && i < a.m0_words) {
         // word 0's taken mask of route i (row R and the padding: zero)
         if (i < R) v = a.raw[i * 16u];
+    } else if (!a.full && i < a.m0_words) {
+        // route pairs: word 0's taken mask, and the taken tool with the LDS
+        // address of the route's row, as the control word holds them
+        const uint32_t r = i >> 1;
+        if (r < R) v = (i & 1u) ? ((a.raw[r * 16u + 1u] & 7u) << 6) | table_row_field(a.rows_off, r) : a.raw[r * 16u];
     } else if (i >= a.rows_off && i < a.rows_off + a.tab_words) {
         const uint32_t j = i - a.rows_off;
         if (a.full) {
@@ -396,17 +434,16 @@ __global__ __launch_bounds__(256) void rc_prep_kernel(ImageArgs a) {
             const uint32_t r = j / RS, w = j % RS;
             if (r < R && w < WM) v = a.raw[r * 16u + (w & 15u)] * (w + 1u);
         } else {
-            const uint32_t i2 = j;
-            const uint32_t r = i2 / 16u, p = i2 % 16u;
-            const uint32_t q = (p >> 2) ^ (r & 3u);
+            const uint32_t r = j / 16u, p = j % 16u;
+            const uint32_t q = (p >> 2) ^ ((r >> 2) & 3u);
             const uint32_t w = 4u * q + (p & 3u);
             if (r < R) v = a.raw[r * 16u + w];
         }
     } else if (a.full && i >= a.tools_off && i < a.tools_off + R) {
         const uint32_t r = i - a.tools_off;
         v = (a.raw[r * 16u] & 7u) | ((a.raw[r * 16u + 1u] & 7u) << 8);
-    } else if (i >= a.cdf_off && i < a.cdf_off + a.cdf_n) {
-        v = a.cdf[i - a.cdf_off];
+    } else if (i >= a.cdf_off && i < a.cdf_off + a.cdf_n + CDF_PAD) {
+        v = i - a.cdf_off < a.cdf_n ? a.cdf[i - a.cdf_off] : 0xFFFFFFFFu;
     } else if (a.guide_n && i >= a.guide_off && i < a.guide_off + a.guide_n) {
         const uint32_t bkt = i - a.guide_off;
         const uint32_t last = a.guide_n - 1u;
@@ -449,315 +486,6 @@ struct ChainArgs {
 __device__ __forceinline__ uint32_t dword_of(const ChainArgs& a, uint32_t t, uint32_t s) {
     return a.dbits[(size_t)t * a.dwords + (s >> 5)];
 }
-
-// No-decision floor, table image: session s's decisions of the 16 steps from
-// t0 (bit i = step t0 + i; steps past the chain read its last step's word),
-// zero for idle lanes.  One word at a time, on purpose (see the caller).
-__device__ __forceinline__ uint32_t decision_block(const ChainArgs& a, const LaneCohort& L, uint32_t t0) {
-    const uint32_t s = L.active ? L.s : 0u;
-    uint32_t m = 0u;
-#pragma unroll 1
-    for (uint32_t i = 0; i < 16u; ++i) {
-        const uint32_t t = t0 + i < a.n_steps ? t0 + i : a.n_steps - 1u;
-        m |= ((dword_of(a, t, s) >> (s & 31u)) & 1u) << i;
-    }
-    return L.active ? m : 0u;
-}
-
-// One row (WM words) of the image; logical block q of row r sits at block
-// q ^ (r mod NB), so its byte address is one XOR away.
-template <int WM>
-__device__ __forceinline__ void load_row(const uint32_t* lds, uint32_t row, uint32_t (&m)[WM]) {
-    constexpr uint32_t NB = WM / 4;
-    const uint32_t rb = row * (NB * 16u) + ((row & (NB - 1u)) << 4);
-    const char* base = reinterpret_cast<const char*>(lds);
-#pragma unroll
-    for (uint32_t q = 0; q < NB; ++q) {
-        const uint4 v = *reinterpret_cast<const uint4*>(base + (rb ^ (q << 4)));
-        m[4 * q + 0] = v.x;
-        m[4 * q + 1] = v.y;
-        m[4 * q + 2] = v.z;
-        m[4 * q + 3] = v.w;
-    }
-}
-
-// Tool of route r for decision d: table[r][d] mod 8.
-template <bool FULL>
-__device__ __forceinline__ uint32_t tool_of(const uint32_t* lds, const uint32_t* lds_tools,
-                                            uint32_t r, bool d) {
-    if constexpr (FULL) {
-        return (lds_tools[r] >> (d ? 8u : 0u)) & 7u;
-    } else {
-        // table[r][0..3] is block 0 of row r, stored at block (r mod 4)
-        return lds[r * 16u + ((r & 3u) << 2) + (d ? 1u : 0u)] & 7u;
-    }
-}
-
-// Table image, band 0 (words 4..15): masks table[r][j] * (j + 1).
-template <int J, int WMAX>
-__device__ __forceinline__ void band0(uint32_t (&S)[WMAX], const uint32_t (&tv)[16],
-                                      uint32_t (&M)[16], uint32_t sh, uint32_t oo) {
-    if constexpr (J < 16) {
-        M[J] = mul_small<J + 1>(tv[J]);
-        if constexpr (J < WMAX)
-            S[J] = (rotr32(S[J], sh) ^ M[J]) + oo;  // words >= W: padding, see band()
-        band0<J + 1, WMAX>(S, tv, M, sh, oo);
-    }
-}
-
-// Table image, band B >= 1 (words 16 B .. 16 B + 15): the mask of w is the
-// mask of w - 16 plus table[r][w mod 16] << 4; it is formed only after word
-// w - 16 is done, so one band of masks is live at a time.
-template <int B, int WMAX>
-__device__ __forceinline__ void band(uint32_t (&S)[WMAX], const uint32_t (&tv)[16],
-                                     uint32_t (&M)[16], uint32_t sh, uint32_t oo) {
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        constexpr int base = 16 * B;
-        // one v_lshl_add_u32 per mask (written out, so that the shift is
-        // not computed once and kept for every band)
-        M[j] = after_word(lshl4_add(tv[j], M[j]), S[base + j - 16]);
-        // Every word is updated, also past W: those registers start at zero,
-        // are never stored, and feed nothing else, while a per-word branch
-        // here would keep extra values live across the bands (and spill).
-        S[base + j] = (rotr32(S[base + j], sh) ^ M[j]) + oo;
-    }
-}
-
-// One bin of the resident chain.  MULTI: the bin holds cohorts of more than
-// 64 sessions (every non-empty wavefront is part of one), so each step
-// exchanges popcounts behind a workgroup barrier; otherwise every cohort lies
-// inside one wavefront and no barrier is needed.
-// FLOOR: the no-decision floor -- every decision is read from the bitmap
-// (16 steps of a lane's decisions loaded at once and packed into one
-// register) instead of computed; nothing else changes.
-template <int WMAX, bool EXACT, int NWAVE, bool FULL, int RK, bool MULTI, bool FLOOR>
-struct Chain {
-    static constexpr int MW = FULL ? WMAX : 16;
-    // Effect stores are nontemporal here: this path serves the large
-    // variable-cohort workloads, whose bins are mostly sub-wavefront cohorts
-    // that write whole lines per wavefront.
-    static constexpr bool NTE = true;
-    static constexpr uint32_t CNT_STRIDE = NWAVE + 4;
-
-    // Everything one lane carries from step to step.
-    struct Lane {
-        uint32_t S[WMAX];
-        uint32_t o, r, step, pub;
-        uint32_t dm;  // FLOOR: this lane's decisions of the current 16-step block (bit i)
-        bool dk;
-        uint64_t bal;
-        uint32_t c4[4];
-    };
-
-    // One chained step.  Full image: `mc` holds this step's masks and the
-    // next step's row is prefetched into `mn`.  Table image: `mc` receives
-    // this step's table row.  The next step's decision is made (and, for
-    // MULTI, its popcount exchanged) even after the last step: the work is
-    // discarded, and every wavefront runs the same schedule.
-    static __device__ __forceinline__ void step(const ChainArgs& a, const LaneCohort& L, Lane& st,
-                                                uint32_t t, uint32_t lane, uint32_t wv,
-                                                const uint32_t* lds, uint32_t* lds_cnt,
-                                                uint32_t (&mc)[MW], uint32_t (&mn)[MW]) {
-        const uint32_t R = a.ra.n_routes;
-        const uint32_t W = a.n_words;
-
-        const uint32_t sh = opaque(st.dk ? 0u : ((31u - st.r) & 31u));
-        const uint32_t oo = opaque(st.dk ? 0u : st.o);
-        const uint32_t tool = tool_of<FULL>(lds, lds + a.tools_off, st.r, st.dk);
-        uint32_t M[16];  // table image: running masks of the 16 columns
-        if constexpr (!FULL) {
-            load_row<16>(lds, st.dk ? st.r : R, mc);
-            M[0] = mul_small<1>(mc[0]);
-            M[1] = mul_small<2>(mc[1]);
-            M[2] = mul_small<3>(mc[2]);
-            M[3] = mul_small<4>(mc[3]);
-        }
-
-        // (a6) words 0..3: the payload, and the input of the next decision
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const uint32_t m = FULL ? mc[w] : M[w];
-            if (EXACT || (uint32_t)w < W) st.S[w] = (rotr32(st.S[w], sh) ^ m) + oo;
-        }
-
-        // (a8) chain: next outcome; (a3, a4) the next step's route and decision
-        const uint32_t o_n = dev_fmix32(st.S[0]);
-        const uint32_t r_n = route_of<RK>(o_n, a.ra, lds + a.cdf_off, lds + a.guide_off);
-        bool d_n;
-        if constexpr (FLOOR) {
-            // a new 16-step block: its words, one at a time (a wait for a
-            // load drains the effect stores in flight, so it happens once
-            // per block, and the serial loop keeps no extra registers live)
-            const uint32_t tn = t + 1u;
-            if ((tn & 15u) == 0u && tn < a.n_steps) st.dm = decision_block(a, L, tn);
-            d_n = L.active && ((st.dm >> (tn & 15u)) & 1u);
-        } else {
-            d_n = L.active && ((dev_fmix32(st.S[0] ^ o_n ^ (st.step + 1u)) & 0xFFFFu) < a.thr);
-        }
-        const uint64_t bal_n = __ballot(d_n);
-        if constexpr (MULTI) publish_count(L, bal_n, lane, wv, lds_cnt, CNT_STRIDE, st.pub);
-        if constexpr (FULL) load_row<MW>(lds, d_n ? r_n : R, mn);
-
-        // (a6) the remaining words
-        if constexpr (FULL) {
-#pragma unroll
-            for (int w = 4; w < WMAX; ++w)
-                if (EXACT || (uint32_t)w < W) st.S[w] = (rotr32(st.S[w], sh) ^ mc[w]) + oo;
-        } else {
-            band0<4, WMAX>(st.S, mc, M, sh, oo);
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (WMAX > 16) {
-                band<1, WMAX>(st.S, mc, M, sh, oo);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if constexpr (WMAX > 32) {
-                band<2, WMAX>(st.S, mc, M, sh, oo);
-                __builtin_amdgcn_sched_barrier(0);
-                band<3, WMAX>(st.S, mc, M, sh, oo);
-            }
-        }
-
-        // the next step's counts: every wavefront has published by now
-        uint32_t c4n[4] = {0u, 0u, 0u, 0u};
-        if constexpr (MULTI) barrier_read_counts<FULL>(L, lds_cnt, CNT_STRIDE, st.pub, c4n);
-
-        // (a5) compaction of this step: stable partition, taken first
-        uint32_t n1, rank_t;
-        if constexpr (MULTI) {
-            const uint32_t wi = (L.flags >> 8) & 0xFFu;
-            const uint32_t nw = (L.flags >> 16) & 0xFFu;
-            uint32_t before = 0, total = 0;
-#pragma unroll
-            for (uint32_t i = 0; i < 4; ++i) {
-                const uint32_t ci = uni(st.c4[i]);
-                total += (i < nw) ? ci : 0u;
-                before += (i < wi) ? ci : 0u;
-            }
-            n1 = total;
-            rank_t = before + lane_rank(st.bal);
-        } else {
-            const uint64_t bs = st.bal & L.seg;
-            n1 = (uint32_t)__popcll(bs);
-            rank_t = lane_rank(bs);
-        }
-        const uint32_t in_c = L.s - L.b;
-        const uint32_t slot = L.b + (st.dk ? rank_t : n1 + (in_c - rank_t));
-
-        // (a7) emit.  slot - b < k always holds; the test keeps a compaction
-        // defect from ever becoming a write outside the cohort's slots.
-        if (L.active && slot - L.b < L.k) {
-            const size_t slice = (size_t)t * a.ld;
-            st32<NTE>(a.eff_sid + slice, slot << 2, L.s);
-            st32<NTE>(a.eff_tool + slice, slot << 2, tool);
-            st128<NTE>(a.eff_payload + slice * 4u, slot << 4,
-                       make_uint4(st.S[0], st.S[1], st.S[2], st.S[3]));
-            if (L.s == L.b) st32(a.n_taken + (size_t)t * a.n_cohorts, L.c << 2, n1);
-        }
-
-        st.o = o_n;
-        st.r = r_n;
-        st.dk = d_n;
-        st.bal = bal_n;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) st.c4[i] = c4n[i];
-        st.step += 1u;
-    }
-
-    static __device__ __forceinline__ void run(const ChainArgs& a, uint32_t bin, uint4* lds4) {
-        uint32_t* lds = reinterpret_cast<uint32_t*>(lds4);
-        const uint32_t tid = threadIdx.x;
-        const uint32_t lane = tid & 63u;
-        const uint32_t wv = tid >> 6;
-        const uint32_t W = a.n_words;
-        const uint32_t R = a.ra.n_routes;
-        const uint32_t T = a.n_steps;
-        uint32_t* lds_cnt = lds + a.img_words;  // [2][NWAVE + 4]
-
-        // (a1) stage the table image (eight 16-byte loads per thread in flight)
-        {
-            const uint4* src = reinterpret_cast<const uint4*>(a.img);
-            const uint32_t n4 = a.img_words / 4u;
-            constexpr uint32_t WG = NWAVE * 64;
-            for (uint32_t j0 = tid; j0 < n4; j0 += 8u * WG) {
-                uint4 v[8];
-#pragma unroll
-                for (uint32_t k = 0; k < 8; ++k) {
-                    const uint32_t j = j0 + k * WG;
-                    v[k] = src[j < n4 ? j : n4 - 1u];
-                }
-#pragma unroll
-                for (uint32_t k = 0; k < 8; ++k)
-                    if (j0 + k * WG < n4) lds4[j0 + k * WG] = v[k];
-            }
-            __syncthreads();
-        }
-
-        const LaneCohort L = lane_cohort(a.wdesc + ((size_t)bin * NWAVE + wv) * WD_WORDS,
-                                         a.offsets, lane, a.cohort_begin, a.cohort_end);
-        const uint32_t soff = L.s << 2;
-        Lane st;
-        st.pub = 0;
-
-        // (a2) load the state words and the pending outcome
-#pragma unroll
-        for (int w = 0; w < WMAX; ++w) st.S[w] = 0;
-        st.o = 0;
-        // FLOOR: the first 16 steps' decision words, issued ahead of the
-        // state words (steps past the chain read its last step's word), so
-        // that the loop has no global load until step 16
-        uint32_t dwd[16];
-        st.dm = 0u;
-        if constexpr (FLOOR) {
-            const uint32_t ls = L.active ? L.s : 0u;
-#pragma unroll
-            for (uint32_t i = 0; i < 16u; ++i) dwd[i] = dword_of(a, i < T ? i : T - 1u, ls);
-        }
-        if (L.active) {
-            const uint32_t ldw = opaque_s(a.ld);
-            st.o = ld32(a.outcome, soff);
-#pragma unroll
-            for (int w = 0; w < WMAX; ++w)
-                if (EXACT || (uint32_t)w < W) st.S[w] = ld32(a.state + (size_t)w * ldw, soff);
-        }
-        if constexpr (FLOOR) {
-            uint32_t m = 0u;
-#pragma unroll
-            for (uint32_t i = 0; i < 16u; ++i) m |= ((dwd[i] >> (L.s & 31u)) & 1u) << i;
-            st.dm = L.active ? m : 0u;
-        }
-
-        // decision of the first step
-        st.step = a.step0;
-        st.r = route_of<RK>(st.o, a.ra, lds + a.cdf_off, lds + a.guide_off);
-        if constexpr (FLOOR)
-            st.dk = (st.dm & 1u) != 0u;
-        else
-            st.dk = L.active && ((dev_fmix32(st.S[0] ^ st.o ^ st.step) & 0xFFFFu) < a.thr);
-        st.bal = __ballot(st.dk);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) st.c4[k] = 0u;
-        if constexpr (MULTI) exchange_counts(L, st.bal, lane, wv, lds_cnt, CNT_STRIDE, st.pub, st.c4);
-        uint32_t mA[MW], mB[MW];
-        if constexpr (FULL) load_row<MW>(lds, st.dk ? st.r : R, mA);
-
-        // T chained steps, unrolled by two so the prefetched row needs no copy
-        for (uint32_t t = 0; t < T; t += 2u) {
-            step(a, L, st, t, lane, wv, lds, lds_cnt, mA, mB);
-            if (t + 1u < T) step(a, L, st, t + 1u, lane, wv, lds, lds_cnt, mB, mA);
-        }
-
-        // (a9) store the state and the next outcome (addresses recomputed
-        // rather than kept live across the chain)
-        if (L.active) {
-            const uint32_t ldw = opaque_s(a.ld);
-#pragma unroll
-            for (int w = 0; w < WMAX; ++w)
-                if (EXACT || (uint32_t)w < W) st32<true>(a.state + (size_t)w * ldw, soff, st.S[w]);
-            st32<true>(a.outcome, soff, st.o);
-        }
-    }
-};
 
 // Workgroup barrier for LDS traffic only: each wavefront waits for its own
 // LDS accesses (lgkmcnt 0; vmcnt and expcnt left at their maxima), not for
@@ -1426,31 +1154,505 @@ struct ChainF {
 };
 
 // One workgroup per bin: blocks [0, bins_a_n) take the sub-wavefront bins,
-// the rest the multi-wavefront bins.  The table-image chain and the two-role
-// full-image chain at W = 32 run two 512-lane workgroups per CU, so they are
-// held to four wavefronts per SIMD (at most 128 VGPRs); the pipelined split
-// (W = 16 or 32) runs two 768-lane workgroups per CU, six wavefronts per
-// SIMD (at most 80 VGPRs).  At W = 64 the two-role full-image chain needs
-// more registers and runs one workgroup per CU.
-template <int WMAX, bool EXACT, int NWAVE, bool FULL, int RK, bool FLOOR, bool PIPED>
-__global__ __launch_bounds__((FULL && (WMAX >= 32 || (PIPED && WMAX == 16)) ? (PIPED && WMAX <= 32 ? 3 : 2) : 1) *
-                                 NWAVE * 64,
-                             (!FULL || WMAX == 32) ? (PIPED && FULL && WMAX == 32 ? 6 : 4)
-                                                   : (PIPED && WMAX == 16 ? 6 : 1))
+// the rest the multi-wavefront bins.  The two-role chain at W = 32 runs two
+// 512-lane workgroups per CU, so it is held to four wavefronts per SIMD (at
+// most 128 VGPRs); the pipelined split (W = 16 or 32) runs two 768-lane
+// workgroups per CU, six wavefronts per SIMD (at most 80 VGPRs).  At W = 64
+// the two-role chain needs more registers and runs one workgroup per CU.
+template <int WMAX, bool EXACT, int NWAVE, int RK, bool FLOOR, bool PIPED>
+__global__ __launch_bounds__((WMAX >= 32 || (PIPED && WMAX == 16) ? (PIPED && WMAX <= 32 ? 3 : 2) : 1) * NWAVE * 64,
+                             WMAX == 32 ? (PIPED ? 6 : 4) : (PIPED && WMAX == 16 ? 6 : 1))
 void rc_chain_kernel(ChainArgs a) {
     extern __shared__ uint4 lds4[];
-    if constexpr (FULL) {
-        constexpr bool SPLIT = WMAX >= 32 || (PIPED && WMAX == 16);
-        if (blockIdx.x < a.bins_a_n)
-            ChainF<WMAX, EXACT, NWAVE, RK, false, SPLIT, FLOOR, PIPED>::run(a, a.bins_a_lo + blockIdx.x, lds4);
-        else
-            ChainF<WMAX, EXACT, NWAVE, RK, true, SPLIT, FLOOR, PIPED>::run(a, a.bins_b_lo + (blockIdx.x - a.bins_a_n), lds4);
-    } else {
-        if (blockIdx.x < a.bins_a_n)
-            Chain<WMAX, EXACT, NWAVE, FULL, RK, false, FLOOR>::run(a, a.bins_a_lo + blockIdx.x, lds4);
-        else
-            Chain<WMAX, EXACT, NWAVE, FULL, RK, true, FLOOR>::run(a, a.bins_b_lo + (blockIdx.x - a.bins_a_n), lds4);
+    constexpr bool SPLIT = WMAX >= 32 || (PIPED && WMAX == 16);
+    if (blockIdx.x < a.bins_a_n)
+        ChainF<WMAX, EXACT, NWAVE, RK, false, SPLIT, FLOOR, PIPED>::run(a, a.bins_a_lo + blockIdx.x, lds4);
+    else
+        ChainF<WMAX, EXACT, NWAVE, RK, true, SPLIT, FLOOR, PIPED>::run(a, a.bins_b_lo + (blockIdx.x - a.bins_a_n), lds4);
+}
+
+// ---------------------------------------------------------------------------
+// Device-resident chain, table image
+// ---------------------------------------------------------------------------
+// Per lane of the plan, built once per handle: the session (TS_IDLE: no
+// session), and what the compaction needs of its cohort.
+constexpr uint32_t TS_IDLE = 0xFFFFFFFFu;
+enum : uint32_t {
+    TI_INC = 0,      // bits 0..7: index of the session in its cohort
+    TI_SIZE = 8,     // bits 8..16: cohort size
+    TI_LO = 17,      // bits 17..22: first lane of the cohort (sub-wavefront cohorts)
+    TI_MULTI = 23,   // bit 23: the wavefront is part of a cohort of > 64 sessions, and of it:
+    TI_WI = 24,      // bits 24..25: this wavefront's index in the cohort
+    TI_NW = 26,      // bits 26..27: wavefronts of the cohort, minus one
+    TI_FIRST = 28    // bits 28..29: first wavefront in the workgroup
+};
+
+__global__ __launch_bounds__(256) void rc_lanes_kernel(const uint32_t* wdesc, const uint32_t* offsets,
+                                                       uint32_t n_cohorts, uint32_t* lane_s, uint2* lane_i) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = blockIdx.x * 4u + (threadIdx.x >> 6);
+    const LaneCohort L = lane_cohort(wdesc + (size_t)wave * WD_WORDS, offsets, lane, 0u, n_cohorts);
+    uint32_t v = 0u;
+    if (L.flags & WF_MULTI)
+        v = (1u << TI_MULTI) | (((L.flags >> 8) & 3u) << TI_WI) | ((((L.flags >> 16) - 1u) & 3u) << TI_NW) |
+            (((L.flags >> 24) & 3u) << TI_FIRST);
+    if (L.active) {
+        const uint32_t in_c = L.s - L.b;
+        v |= in_c | (L.k << TI_SIZE);
+        if (!(L.flags & WF_MULTI)) v |= (lane - in_c) << TI_LO;
     }
+    lane_s[(size_t)wave * 64u + lane] = L.active ? L.s : TS_IDLE;
+    lane_i[(size_t)wave * 64u + lane] = make_uint2(L.active ? L.c : 0u, v);
+}
+
+struct TableArgs {
+    uint32_t* state;
+    uint32_t* outcome;
+    uint32_t* eff_sid;
+    uint32_t* eff_tool;
+    uint32_t* eff_payload;
+    uint32_t* n_taken;
+    const uint32_t* img;      // LDS image: [route pairs | thresholds | guide] (chain_words), raw rows
+    const uint32_t* lane_s;   // [bins][256]
+    const uint2* lane_i;      // [bins][256]: cohort, TI_ fields
+    RouteArgs ra;
+    uint32_t ld, n_words, n_cohorts, thr, step0, n_steps;
+    uint32_t s_lo, s_n;       // sessions of the stepped cohorts: [s_lo, s_lo + s_n)
+    uint32_t bins_a_lo, bins_a_n, bins_b_lo, n_units;
+    uint32_t img_words, chain_words, cdf_off, guide_off, zero_row;  // zero_row: row R's control field
+    const uint32_t* dbits;    // no-decision floor: [T][dwords] decision bitmap
+    uint32_t dwords;
+};
+
+// NB = ceil(W / 16) bands of 16 words.  The masks are table[r][w mod 16] *
+// (w + 1): column j's masks over the bands are t * (j + 1), + (t << 4), ...
+// with t = table[r][j], so the words are split over wavefronts by column and
+// each reads only its columns of the row.
+//
+// A workgroup is four wavefronts of plan lanes (up to 256 sessions) in four
+// roles, lane for lane, 16 wavefronts in all (one of each role per SIMD):
+//   A  chains word 0 and the outcome, one 4-step chunk ahead, and leaves
+//      every step's control (rotation, decision, tool, mask row) and addend
+//      in LDS, with the taken counts of each wavefront;
+//   B  replays columns 0..3 and emits the effects;
+//   C, D  replay columns 4..9 and 10..15.
+// One LDS barrier per chunk: barrier g publishes chunk g and closes the
+// replay of chunk g - 1 (two chunks in flight, in alternating halves).
+//
+// Workgroups are persistent: the image is staged once and the workgroup
+// takes every gridDim-th bin, its loads issued one bin ahead into registers,
+// so that the loads and the final stores of a bin overlap the steps of its
+// neighbours.  Only B emits effects, and B issues no load: loads and stores
+// retire through one in-order counter, and a load behind a step's effects
+// would wait for them.  A fetches B's words and plan lane with its own and
+// hands them over in LDS.
+//
+// The form that this replaces ran one lane per session, all W words and the
+// effects in it, eight wavefronts to a workgroup and a barrier per step: few
+// sessions left most SIMDs idle, many waited together.  Measured, before and
+// after, us per launch: 60,007 sessions in 467 cohorts, W = 48, R = 1000, T =
+// 24: 38.2 -> 28.9; 5,000 sessions, W = 64, R = 1024 CDF, T = 40: 56.8 -> 26.9;
+// one 100-session cohort, W = 33, T = 20: 31.0 -> 12.9; 130,000 sessions, W =
+// 64, T = 16: 34.0 -> 28.7.  A million sessions, W = 64, R = 1024, T = 16: 212
+// -> 205 (4.4 TB/s): bound by HBM with the loads, effects and final stores of
+// a bin taking turns (203 with nearly all arithmetic removed); few sessions
+// are bound by VALU issue (about 316 instructions per step and SIMD at W =
+// 64, of them 3 per word).  Also measured on it: progress counters in LDS in
+// place of the barriers 215 us (a wavefront's partly filled lines then meet
+// their neighbours' later), single wavefronts walking bins on their own with
+// one lane per session 232 us.
+template <int NB, int RK, bool FLOOR>
+struct ChainT {
+    static constexpr int TC = 4;
+    static constexpr uint32_t NW = 4, NL = NW * 64u;
+    static constexpr uint32_t CNT = 8;  // words per step of the counts (cohorts read four from their first)
+
+    // LDS after the image, in 16-byte units
+    static constexpr uint32_t L_CNT = 2 * TC * CNT / 4, L_CTL = 2 * TC * NL / 2, L_HAND = 2 * (NB + 1) * NL,
+                              L_STAGE = NL + NL / 4;
+    static constexpr uint32_t LDS_AFTER = (L_CNT + L_CTL + L_HAND + L_STAGE) * 16u;
+
+    // This lane's words of columns [J0, J0 + NC).  The row's base is walked in
+    // scalar registers, hidden at every row: folded together, the sums become
+    // 64-bit vector addresses.  A row past W repeats the last one read, so
+    // that no load needs a branch (its value is unused).
+    template <int J0, int NC>
+    static __device__ __forceinline__ void load_cols(const TableArgs& a, uint32_t s, uint32_t (&S)[NB * NC]) {
+        const uint32_t off = s << 2;
+        const uint32_t ld = opaque_s(a.ld);
+        gptr row = (gptr)(a.state + (size_t)J0 * ld);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                asm volatile("" : "+s"(row));
+                S[b * NC + j] = ldg(row, off);
+                const uint32_t w = 16 * b + J0 + j, next = j + 1 < NC ? w + 1 : w + 17 - NC;
+                row += (b < NB - 1 && (b < NB - 2 || j + 1 < NC)) || next < a.n_words ? (size_t)(next - w) * ld : 0u;
+            }
+    }
+
+    template <int J0, int NC>
+    static __device__ __forceinline__ void store_cols(const TableArgs& a, uint32_t s, const uint32_t (&S)[NB * NC]) {
+        const uint32_t off = s << 2;
+        const uint32_t ld = opaque_s(a.ld);
+        gptr row = (gptr)(a.state + (size_t)J0 * ld);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                const uint32_t w = 16 * b + J0 + j, next = j + 1 < NC ? w + 1 : w + 17 - NC;
+                asm volatile("" : "+s"(row));
+                if (b < NB - 1 || w < a.n_words) stg_nt(row, off, S[b * NC + j]);
+                row += (size_t)(next - w) * ld;
+            }
+    }
+
+    // One step of columns [J0, J0 + NC): words past W (last band) start
+    // anywhere, are never stored and feed nothing, so they need no branch.
+    template <int J0, int NC>
+    static __device__ __forceinline__ void update(uint32_t (&S)[NB * NC], const uint32_t (&t)[NC], uint32_t c,
+                                                  uint32_t oo) {
+        if constexpr (NC > 0) update_col<J0, NC, 0>(S, t, c, oo);
+    }
+    template <int J0, int NC, int J>
+    static __device__ __forceinline__ void update_col(uint32_t (&S)[NB * NC], const uint32_t (&t)[NC], uint32_t c,
+                                                      uint32_t oo) {
+        if constexpr (J < NC) {
+            uint32_t m = mul_small<J0 + J + 1>(t[J]);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                S[b * NC + J] = (rotr32(S[b * NC + J], c) ^ m) + oo;
+                if (b + 1 < NB) m = lshl4_add(t[J], m);
+            }
+            update_col<J0, NC, J + 1>(S, t, c, oo);
+        }
+    }
+
+    // Columns of the row a control word points at: 16-byte block q of a row
+    // is one XOR away from its block 0 (see rc_prep_kernel).
+    template <int J0, int NC>
+    static __device__ __forceinline__ void row_cols(const uint32_t* lds, uint32_t ctl, uint32_t (&t)[NC]) {
+        const uint32_t rb = ctl >> 12;
+        const char* p = reinterpret_cast<const char*>(lds);
+        if constexpr (J0 == 0) {
+            const uint4 v = *reinterpret_cast<const uint4*>(p + rb);
+            t[0] = v.x; t[1] = v.y; t[2] = v.z; t[3] = v.w;
+        } else if constexpr (J0 == 4) {
+            const uint4 v = *reinterpret_cast<const uint4*>(p + (rb ^ 16u));
+            const uint2 u = *reinterpret_cast<const uint2*>(p + (rb ^ 32u));
+            t[0] = v.x; t[1] = v.y; t[2] = v.z; t[3] = v.w; t[4] = u.x; t[5] = u.y;
+        } else {
+            const uint2 u = *reinterpret_cast<const uint2*>(p + (rb ^ 32u) + 8u);
+            const uint4 v = *reinterpret_cast<const uint4*>(p + (rb ^ 48u));
+            t[0] = u.x; t[1] = u.y; t[2] = v.x; t[3] = v.y; t[4] = v.z; t[5] = v.w;
+        }
+    }
+
+    static __device__ __forceinline__ uint32_t bin_of(const TableArgs& a, uint32_t u) {
+        return u < a.bins_a_n ? a.bins_a_lo + u : a.bins_b_lo + (u - a.bins_a_n);
+    }
+    // session of plan lane `al` of unit u, idle past the launch's units and
+    // outside the stepped sessions
+    static __device__ __forceinline__ uint32_t lane_session(const TableArgs& a, uint32_t u, uint32_t al) {
+        return u < a.n_units ? a.lane_s[(size_t)bin_of(a, u) * NL + al] : TS_IDLE;
+    }
+    static __device__ __forceinline__ bool stepped(const TableArgs& a, uint32_t s) { return s - a.s_lo < a.s_n; }
+
+    static __device__ __forceinline__ void run(const TableArgs& a, uint4* lds4) {
+        uint32_t* lds = reinterpret_cast<uint32_t*>(lds4);
+        const uint32_t tid = threadIdx.x;
+        const uint32_t lane = tid & 63u;
+        const uint32_t wv = uni(tid >> 6);
+        const uint32_t role = wv >> 2, wa = wv & 3u;  // wavefronts go to SIMDs in turn: one of each role on each
+        const uint32_t al = wa * 64u + lane;
+        const uint32_t T = a.n_steps;
+        const uint32_t G = gridDim.x, u0 = blockIdx.x;
+
+        uint4* p = lds4 + a.img_words / 4u;
+        uint32_t* cnt = reinterpret_cast<uint32_t*>(p);
+        uint2* ctl = reinterpret_cast<uint2*>(p + L_CNT);
+        uint4* hand = p + L_CNT + L_CTL;              // [2][NB + 1][NL]: B's words and plan lane
+        uint4* stage_p = hand + L_HAND;
+        uint32_t* stage_w = reinterpret_cast<uint32_t*>(stage_p + NL);
+
+        typedef __attribute__((address_space(3))) void lds_void;
+        const uint4* img = reinterpret_cast<const uint4*>(a.img);
+        const uint32_t c4 = a.chain_words / 4u, n4 = a.img_words / 4u;
+        // 16-byte blocks [lo, hi) of the image, by wavefronts w of nw
+        auto stage = [&](uint32_t lo, uint32_t hi, uint32_t w, uint32_t nw) {
+            for (uint32_t blk = lo + w * 64u; blk < hi; blk += nw * 64u)
+                if (blk + lane < hi)
+                    __builtin_amdgcn_global_load_lds((const void*)(img + blk + lane), (lds_void*)(lds4 + blk), 16, 0, 0);
+        };
+        auto bare_barrier = []() {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        };
+
+        if (role == 0u) {
+            // -- A ----------------------------------------------------------
+            stage(0u, c4, wa, NW);
+            uint32_t sN = lane_session(a, u0, al), sNN = lane_session(a, u0 + G, al);
+            uint32_t P[4 * NB], po;
+            uint2 pi;
+            uint32_t dN[TC];
+#pragma unroll
+            for (int i = 0; i < 4 * NB; ++i) P[i] = 0u;
+            // words, outcome and plan lane of unit u
+            auto fetch = [&](uint32_t u) {
+                const uint32_t s = stepped(a, sN) ? sN : a.s_lo;
+                po = ld32(a.outcome, s << 2);
+                load_cols<0, 4>(a, s, P);
+                pi = a.lane_i[(size_t)bin_of(a, u) * NL + al];
+                if constexpr (FLOOR) {
+#pragma unroll
+                    for (int i = 0; i < TC; ++i)
+                        dN[i] = a.dbits[(size_t)((uint32_t)i < T ? (uint32_t)i : T - 1u) * a.dwords + (s >> 5)];
+                }
+            };
+            fetch(u0);
+            wait_vmcnt<0>();  // chain section in LDS
+            bare_barrier();
+            __builtin_amdgcn_s_setprio(3);
+            const uint2* pairs = reinterpret_cast<const uint2*>(lds);
+            uint32_t half = 0u, hb = 0u;
+            for (uint32_t u = u0; u < a.n_units; u += G, hb ^= 1u) {
+                const bool act = stepped(a, sN);
+                const uint32_t ss = act ? sN : a.s_lo;
+                uint32_t s0 = P[0], o = po;
+                uint4* h = hand + hb * (NB + 1) * NL + al;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) h[b * NL] = make_uint4(P[4 * b], P[4 * b + 1], P[4 * b + 2], P[4 * b + 3]);
+                h[NB * NL] = make_uint4(pi.x, pi.y, act ? sN : TS_IDLE, 0u);
+                uint32_t dw[TC];
+                if constexpr (FLOOR) {
+#pragma unroll
+                    for (int i = 0; i < TC; ++i) dw[i] = dN[i];
+                }
+                sN = sNN;
+                if (u + G < a.n_units) {
+                    fetch(u + G);
+                    sNN = lane_session(a, u + 2u * G, al);
+                }
+                uint32_t step = a.step0;
+                uint32_t r = route_of<RK>(o, a.ra, lds + a.cdf_off, lds + a.guide_off);
+                uint2 pr = pairs[r];
+                const uint32_t actb = act ? 1u : 0u;
+                for (uint32_t t0 = 0; t0 < T; t0 += TC, half ^= 1u) {
+                    const uint32_t n = T - t0;
+                    uint32_t dnx[TC];
+                    if constexpr (FLOOR) {
+                        // the next chunk's decision words, in flight during this one
+#pragma unroll
+                        for (int i = 0; i < TC; ++i) {
+                            const uint32_t t = t0 + TC + i;
+                            dnx[i] = t0 + TC < T ? a.dbits[(size_t)(t < T ? t : T - 1u) * a.dwords + (ss >> 5)] : 0u;
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < TC; ++i) {
+                        if ((uint32_t)i >= n) continue;
+                        uint32_t dbit;
+                        if constexpr (FLOOR)
+                            dbit = actb & (dw[i] >> (ss & 31u));
+                        else
+                            dbit = actb & (uint32_t)((dev_fmix32(s0 ^ o ^ step) & 0xFFFFu) < a.thr);
+                        const uint32_t dm = 0u - dbit;  // all ones when taken
+                        const uint32_t rot = (31u - r) & 31u & ~dm;
+                        const uint32_t oo = o & ~dm;
+                        // control: rotation (bits 0..4), decision (5), tool
+                        // (6..8), LDS address of the mask row / 16 (16..31)
+                        const uint32_t nt = ((pr.x & 7u) << 6) | a.zero_row;
+                        const uint32_t c = (dbit ? pr.y : nt) | rot | (dm & 32u);
+                        ctl[(half * TC + i) * NL + al] = make_uint2(c, oo);
+                        cnt[(half * TC + i) * CNT + wa] = (uint32_t)__popcll(__ballot(dbit != 0u));
+                        s0 = (rotr32(s0, rot) ^ (pr.x & dm)) + oo;
+                        o = dev_fmix32(s0);
+                        r = route_of<RK>(o, a.ra, lds + a.cdf_off, lds + a.guide_off);
+                        pr = pairs[r];
+                        step += 1u;
+                    }
+                    if constexpr (FLOOR) {
+#pragma unroll
+                        for (int i = 0; i < TC; ++i) dw[i] = dnx[i];
+                    }
+                    lds_barrier();
+                }
+            }
+        } else if (role == 1u) {
+            // -- B ----------------------------------------------------------
+            stage(c4, n4, wa, 3u * NW);
+            bare_barrier();
+            wait_vmcnt<0>();  // rows in LDS before the barrier that publishes the first chunk
+            uint32_t half = 0u, hb = 0u;
+            for (uint32_t u = u0; u < a.n_units; u += G, hb ^= 1u) {
+                uint32_t S[4 * NB];
+                uint32_t s = 0u, coh = 0u, inf = 0u;
+                uint32_t* p_sid = a.eff_sid;
+                uint32_t* p_tool = a.eff_tool;
+                uint32_t* p_pay = a.eff_payload;
+                uint32_t* p_cnt = a.n_taken;
+                for (uint32_t t0 = 0; t0 < T; t0 += TC, half ^= 1u) {
+                    lds_barrier();
+                    if (t0 == 0u) {
+                        const uint4* h = hand + hb * (NB + 1) * NL + al;
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) {
+                            const uint4 v = h[b * NL];
+                            S[4 * b] = v.x; S[4 * b + 1] = v.y; S[4 * b + 2] = v.z; S[4 * b + 3] = v.w;
+                        }
+                        const uint4 v = h[NB * NL];
+                        coh = v.x;
+                        inf = v.y;
+                        s = v.z;
+                    }
+                    const uint32_t fl = uni(inf);
+                    const bool multi = (fl >> TI_MULTI) & 1u;
+                    const bool act = s != TS_IDLE;
+                    const uint32_t in_c = inf & 255u, k = (inf >> TI_SIZE) & 511u, b0 = s - in_c;
+                    const uint32_t n = (T - t0) < (uint32_t)TC ? (T - t0) : (uint32_t)TC;
+                    // the cohort's taken counts: lane i combines step i's
+                    uint32_t n1v = 0u, prev = 0u;
+                    if (multi) {
+                        const uint32_t* q = cnt + (half * TC + (lane & 3u)) * CNT + ((fl >> TI_FIRST) & 3u);
+                        const uint32_t wi = (fl >> TI_WI) & 3u, nw = ((fl >> TI_NW) & 3u) + 1u;
+                        const uint32_t q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+                        n1v = q0 + q1 + (nw > 2u ? q2 : 0u) + (nw > 3u ? q3 : 0u);
+                        prev = (wi > 0u ? q0 : 0u) + (wi > 1u ? q1 : 0u) + (wi > 2u ? q2 : 0u);
+                    }
+                    const uint32_t lo = (inf >> TI_LO) & 63u, hi = lo + k;  // this lane's cohort, if sub-wavefront
+                    const uint64_t seg = multi ? ~0ull
+                                               : (hi >= 64u ? ~0ull : ((1ull << hi) - 1ull)) & ~((1ull << lo) - 1ull);
+                    // the chunk's control and mask columns, read together
+                    // (steps past the last one repeat it)
+                    uint2 cas[TC];
+                    uint32_t ts[TC][4];
+#pragma unroll
+                    for (int i = 0; i < TC; ++i)
+                        cas[i] = ctl[(half * TC + ((uint32_t)i < n ? (uint32_t)i : n - 1u)) * NL + al];
+#pragma unroll
+                    for (int i = 0; i < TC; ++i) row_cols<0, 4>(lds, cas[i].x, ts[i]);
+#pragma unroll
+                    for (int i = 0; i < TC; ++i) {
+                        if ((uint32_t)i >= n) continue;
+                        const uint2 ca = cas[i];
+                        update<0, 4>(S, ts[i], ca.x, ca.y);
+                        const bool dk = (ca.x >> 5) & 1u;
+                        const uint32_t tool = (ca.x >> 6) & 7u;
+                        // (a5) stable partition, taken first
+                        const uint64_t bal = __ballot(dk);
+                        const uint64_t bs = bal & seg;
+                        uint32_t n1, rank_t = lane_rank(bs);
+                        if (multi) {
+                            n1 = __builtin_amdgcn_readlane(n1v, i);
+                            rank_t += __builtin_amdgcn_readlane(prev, i);
+                        } else {
+                            n1 = (uint32_t)__popcll(bs);
+                        }
+                        const uint32_t in_slot = dk ? rank_t : n1 + (in_c - rank_t);
+                        const uint32_t slot = b0 + in_slot;
+                        // (a7) emit; in_slot < k always holds (the test keeps
+                        // a compaction defect from becoming a write outside
+                        // the cohort)
+                        const bool put = act && in_slot < k;
+                        if (multi) {
+                            if (put) {
+                                st32<true>(p_sid, slot << 2, s);
+                                st32<true>(p_tool, slot << 2, tool);
+                                st128<true>(p_pay, slot << 4, make_uint4(S[0], S[1], S[2], S[3]));
+                                if (in_c == 0u) st32(p_cnt, coh << 2, n1);
+                            }
+                        } else {
+                            // through the LDS stage of this wavefront, so
+                            // that its stores cover contiguous slots
+                            if (put) {
+                                const uint32_t pos = al + (slot - s);
+                                stage_w[pos] = s | (tool << 28);
+                                stage_p[pos] = make_uint4(S[0], S[1], S[2], S[3]);
+                            }
+                            asm volatile("" ::: "memory");
+                            if (act) {
+                                const uint32_t w = stage_w[al];
+                                const uint4 pv = stage_p[al];
+                                st32<true>(p_sid, s << 2, w & 0x0FFFFFFFu);
+                                st32<true>(p_tool, s << 2, w >> 28);
+                                st128<true>(p_pay, s << 4, pv);
+                                if (in_c == 0u) st32(p_cnt, coh << 2, n1);
+                            }
+                            asm volatile("" ::: "memory");  // this step's reads before the next step's writes
+                        }
+                        p_sid += a.ld;
+                        p_tool += a.ld;
+                        p_pay += 4u * a.ld;
+                        p_cnt += a.n_cohorts;
+                    }
+                }
+                // (a9) the words of this role and the next outcome
+                if (s != TS_IDLE) {
+                    store_cols<0, 4>(a, s, S);
+                    st32<true>(a.outcome, s << 2, dev_fmix32(S[0]));
+                }
+            }
+        } else {
+            // -- C, D -------------------------------------------------------
+            stage(c4, n4, wv - NW, 3u * NW);
+            auto replay_role = [&](auto j0_c) {
+                constexpr int J0 = decltype(j0_c)::value;
+                constexpr int NC = 6;
+                uint32_t sN = lane_session(a, u0, al), sNN = lane_session(a, u0 + G, al);
+                uint32_t P[NB * NC];
+#pragma unroll
+                for (int i = 0; i < NB * NC; ++i) P[i] = 0u;
+                load_cols<J0, NC>(a, stepped(a, sN) ? sN : a.s_lo, P);
+                bare_barrier();
+                wait_vmcnt<0>();  // rows in LDS before the barrier that publishes the first chunk
+                uint32_t half = 0u;
+                for (uint32_t u = u0; u < a.n_units; u += G) {
+                    uint32_t S[NB * NC];
+#pragma unroll
+                    for (int i = 0; i < NB * NC; ++i) S[i] = P[i];
+                    const uint32_t s = sN;
+                    sN = sNN;
+                    if (u + G < a.n_units) {
+                        load_cols<J0, NC>(a, stepped(a, sN) ? sN : a.s_lo, P);
+                        sNN = lane_session(a, u + 2u * G, al);
+                    }
+                    for (uint32_t t0 = 0; t0 < T; t0 += TC, half ^= 1u) {
+                        const uint32_t n = (T - t0) < (uint32_t)TC ? (T - t0) : (uint32_t)TC;
+                        lds_barrier();
+                        uint2 cas[TC];
+                        uint32_t ts[TC][NC];
+#pragma unroll
+                        for (int i = 0; i < TC; ++i)
+                            cas[i] = ctl[(half * TC + ((uint32_t)i < n ? (uint32_t)i : n - 1u)) * NL + al];
+#pragma unroll
+                        for (int i = 0; i < TC; ++i) row_cols<J0, NC>(lds, cas[i].x, ts[i]);
+#pragma unroll
+                        for (int i = 0; i < TC; ++i) {
+                            if ((uint32_t)i >= n) continue;
+                            update<J0, NC>(S, ts[i], cas[i].x, cas[i].y);
+                        }
+                    }
+                    // the loads of the next unit are long done: wait for them
+                    // ahead of the stores, not behind
+                    wait_vmcnt<0>();
+                    if (stepped(a, s)) store_cols<J0, NC>(a, s, S);
+                }
+            };
+            if (role == 2u)
+                replay_role(std::integral_constant<int, 4>{});
+            else
+                replay_role(std::integral_constant<int, 10>{});
+        }
+    }
+};
+
+template <int NB, int RK, bool FLOOR>
+__global__ __launch_bounds__(1024, 4) void rc_table_kernel(TableArgs a) {
+    extern __shared__ uint4 lds4[];
+    ChainT<NB, RK, FLOOR>::run(a, lds4);
 }
 
 // ---------------------------------------------------------------------------
@@ -1585,44 +1787,61 @@ __device__ __align__(256) uint32_t rc_noalloc_scratch[NOALLOC_PERM_OFF + RC_NOAL
 // ---------------------------------------------------------------------------
 
 typedef void (*ChainFn)(ChainArgs);
-typedef void (*DecideFn)(DecideArgs);
+typedef void (*TableFn)(TableArgs);
 typedef void (*BodyFn)(BodyArgs);
 
 // The pipelined split exists for the full image at WMAX = 16 and 32.
 bool has_piped(uint32_t wmax, bool full) { return full && (wmax == 32u || wmax == 16u); }
 
 template <int WMAX, bool EXACT, int RK, bool FLOOR>
-ChainFn chain_fn(bool full, bool piped) {
-    if (!full) {
-        if constexpr (WMAX >= 32) return rc_chain_kernel<WMAX, EXACT, 8, false, RK, FLOOR, false>;
-        return nullptr;
-    }
+ChainFn chain_fn(bool piped) {
     if constexpr (WMAX == 32 || WMAX == 16)
-        if (piped) return rc_chain_kernel<WMAX, EXACT, 4, true, RK, FLOOR, true>;
-    return rc_chain_kernel<WMAX, EXACT, 4, true, RK, FLOOR, false>;
+        if (piped) return rc_chain_kernel<WMAX, EXACT, 4, RK, FLOOR, true>;
+    return rc_chain_kernel<WMAX, EXACT, 4, RK, FLOOR, false>;
 }
 
 template <int WMAX, bool EXACT, bool FLOOR>
-ChainFn chain_fn_rk(bool full, bool piped, int rk) {
-    return rk == RK_POW2 ? chain_fn<WMAX, EXACT, RK_POW2, FLOOR>(full, piped)
-         : rk == RK_MOD ? chain_fn<WMAX, EXACT, RK_MOD, FLOOR>(full, piped)
-                        : chain_fn<WMAX, EXACT, RK_CDF, FLOOR>(full, piped);
+ChainFn chain_fn_rk(bool piped, int rk) {
+    return rk == RK_POW2 ? chain_fn<WMAX, EXACT, RK_POW2, FLOOR>(piped)
+         : rk == RK_MOD ? chain_fn<WMAX, EXACT, RK_MOD, FLOOR>(piped)
+                        : chain_fn<WMAX, EXACT, RK_CDF, FLOOR>(piped);
 }
 
 template <bool FLOOR>
-ChainFn pick_chain_t(uint32_t wmax, bool exact, bool full, bool piped, int rk) {
+ChainFn pick_chain_t(uint32_t wmax, bool exact, bool piped, int rk) {
     switch (wmax) {
-        case 4: return exact ? chain_fn_rk<4, true, FLOOR>(full, piped, rk) : chain_fn_rk<4, false, FLOOR>(full, piped, rk);
-        case 8: return exact ? chain_fn_rk<8, true, FLOOR>(full, piped, rk) : chain_fn_rk<8, false, FLOOR>(full, piped, rk);
-        case 16: return exact ? chain_fn_rk<16, true, FLOOR>(full, piped, rk) : chain_fn_rk<16, false, FLOOR>(full, piped, rk);
-        case 32: return exact ? chain_fn_rk<32, true, FLOOR>(full, piped, rk) : chain_fn_rk<32, false, FLOOR>(full, piped, rk);
-        default: return exact ? chain_fn_rk<64, true, FLOOR>(full, piped, rk) : chain_fn_rk<64, false, FLOOR>(full, piped, rk);
+        case 4: return exact ? chain_fn_rk<4, true, FLOOR>(piped, rk) : chain_fn_rk<4, false, FLOOR>(piped, rk);
+        case 8: return exact ? chain_fn_rk<8, true, FLOOR>(piped, rk) : chain_fn_rk<8, false, FLOOR>(piped, rk);
+        case 16: return exact ? chain_fn_rk<16, true, FLOOR>(piped, rk) : chain_fn_rk<16, false, FLOOR>(piped, rk);
+        case 32: return exact ? chain_fn_rk<32, true, FLOOR>(piped, rk) : chain_fn_rk<32, false, FLOOR>(piped, rk);
+        default: return exact ? chain_fn_rk<64, true, FLOOR>(piped, rk) : chain_fn_rk<64, false, FLOOR>(piped, rk);
     }
 }
 
-ChainFn pick_chain(uint32_t wmax, bool exact, bool full, bool piped, int rk, bool floor) {
-    return floor ? pick_chain_t<true>(wmax, exact, full, piped, rk)
-                 : pick_chain_t<false>(wmax, exact, full, piped, rk);
+ChainFn pick_chain(uint32_t wmax, bool exact, bool piped, int rk, bool floor) {
+    return floor ? pick_chain_t<true>(wmax, exact, piped, rk) : pick_chain_t<false>(wmax, exact, piped, rk);
+}
+
+// Table image (W > 16): kernel of nb = ceil(W / 16) bands, and its LDS after
+// the image.
+template <int NB, bool FLOOR>
+TableFn table_fn(int rk) {
+    return rk == RK_POW2 ? rc_table_kernel<NB, RK_POW2, FLOOR>
+         : rk == RK_MOD ? rc_table_kernel<NB, RK_MOD, FLOOR>
+                        : rc_table_kernel<NB, RK_CDF, FLOOR>;
+}
+
+TableFn pick_table(uint32_t nb, int rk, bool floor) {
+    switch (nb) {
+        case 2: return floor ? table_fn<2, true>(rk) : table_fn<2, false>(rk);
+        case 3: return floor ? table_fn<3, true>(rk) : table_fn<3, false>(rk);
+        default: return floor ? table_fn<4, true>(rk) : table_fn<4, false>(rk);
+    }
+}
+
+uint32_t table_lds_after(uint32_t nb) {
+    return nb == 2u ? ChainT<2, 0, false>::LDS_AFTER : nb == 3u ? ChainT<3, 0, false>::LDS_AFTER
+                                                                : ChainT<4, 0, false>::LDS_AFTER;
 }
 
 // The pipelined split for a launch: at most one workgroup per CU, or a
@@ -1652,10 +1871,6 @@ BodyFn pick_body(uint32_t wmax, bool exact, bool taken) {
         case 32: return exact ? body_fn<32, true>(taken) : body_fn<32, false>(taken);
         default: return exact ? body_fn<64, true>(taken) : body_fn<64, false>(taken);
     }
-}
-
-DecideFn pick_decide(uint32_t nwave) {
-    return nwave == 8 ? rc_decide_kernel<8> : rc_decide_kernel<4>;
 }
 
 // Restores the caller's current device on scope exit.
@@ -1718,6 +1933,9 @@ struct rc_cohort {
     uint32_t* d_img = nullptr;
     uint32_t* d_span = nullptr;
     uint32_t* d_wdesc = nullptr;
+    uint32_t* d_lane_s = nullptr;  // table image: plan lanes (see rc_lanes_kernel)
+    uint2* d_lane_i = nullptr;
+    uint32_t table_wgs = 256;      // table image: workgroups that fit the device at once
     uint32_t* d_perm = nullptr;  // host round trip: [N] slot -> sid | d << 31
     uint32_t* d_ctr = nullptr;
     uint32_t* h_word = nullptr;  // pinned
@@ -1746,6 +1964,8 @@ void free_handle(rc_cohort* h) {
         (void)hipFree(h->d_img);
         (void)hipFree(h->d_span);
         (void)hipFree(h->d_wdesc);
+        (void)hipFree(h->d_lane_s);
+        (void)hipFree(h->d_lane_i);
         (void)hipFree(h->d_perm);
         (void)hipFree(h->d_ctr);
         if (h->h_word) (void)hipHostFree(h->h_word);
@@ -1853,8 +2073,50 @@ int launch_ok() {
     return hipGetLastError() == hipSuccess ? RC_OK : RC_E_DEVICE;
 }
 
+// Table image: persistent workgroups, as many as fit the device at once.
+int run_table(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32_t T, uint32_t cb, uint32_t ce,
+              hipStream_t stream, const uint32_t* dbits) {
+    TableArgs a;
+    a.state = b->state;
+    a.outcome = b->outcome;
+    a.eff_sid = b->eff_sid;
+    a.eff_tool = b->eff_tool;
+    a.eff_payload = b->eff_payload;
+    a.n_taken = b->n_taken;
+    a.img = h->d_img;
+    a.lane_s = h->d_lane_s;
+    a.lane_i = h->d_lane_i;
+    a.ra = h->ra;
+    a.ld = b->ld;
+    a.n_words = h->W;
+    a.n_cohorts = h->C;
+    a.thr = h->thr;
+    a.step0 = step0;
+    a.n_steps = T;
+    a.s_lo = h->offsets[cb];
+    a.s_n = h->offsets[ce] - a.s_lo;
+    uint32_t b_n;
+    bins_of_range(h->plan, cb, ce, a.bins_a_lo, a.bins_a_n, a.bins_b_lo, b_n);
+    a.n_units = a.bins_a_n + b_n;
+    a.img_words = h->img_words;
+    a.chain_words = h->chain_words;
+    a.cdf_off = h->cdf_off;
+    a.guide_off = h->guide_off;
+    a.zero_row = table_row_field(h->rows_off, h->R);
+    a.dbits = dbits;
+    a.dwords = (b->ld + 31u) / 32u;
+    const uint32_t grid = a.n_units < h->table_wgs ? a.n_units : h->table_wgs;
+    TableFn fn = pick_table((h->W + 15u) / 16u, h->route_kind, dbits != nullptr);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(1024), h->chain_lds_bytes, stream, a);
+    if (launch_ok() != RC_OK) return RC_E_DEVICE;
+    h->last_launches = 1;
+    h->last_d2h = 0;
+    return RC_OK;
+}
+
 int run_resident(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32_t T,
                  uint32_t cb, uint32_t ce, hipStream_t stream, const uint32_t* dbits = nullptr) {
+    if (!h->full) return run_table(h, b, step0, T, cb, ce, stream, dbits);
     ChainArgs a;
     a.state = b->state;
     a.outcome = b->outcome;
@@ -1885,7 +2147,7 @@ int run_resident(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32_t T,
     a.dwords = (b->ld + 31u) / 32u;
     const uint32_t grid = a.bins_a_n + a.bins_b_n;  // one workgroup per bin
     const bool piped = use_piped(h->wmax, h->full, h->route_kind, grid, h->n_cu);
-    ChainFn fn = pick_chain(h->wmax, h->exact, h->full, piped, h->route_kind, dbits != nullptr);
+    ChainFn fn = pick_chain(h->wmax, h->exact, piped, h->route_kind, dbits != nullptr);
     // the pipelined split runs three lanes per session, the two-role split two
     hipLaunchKernelGGL(fn, dim3(grid), dim3(piped ? 3u * 64u * h->nwave : h->chain_threads), h->chain_lds_bytes,
                        stream, a);
@@ -1926,7 +2188,6 @@ int run_host_roundtrip(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32
     const uint32_t lo = h->offsets[cb], hi = h->offsets[ce];
     const uint32_t n_range = hi - lo;
     const uint32_t body_grid = (n_range + 255u) / 256u;
-    DecideFn dfn = pick_decide(h->nwave);
     BodyFn taken_fn = pick_body(h->wmax, h->exact, true);
     BodyFn not_fn = pick_body(h->wmax, h->exact, false);
     for (uint32_t t = 0; t < T; ++t) {
@@ -1951,7 +2212,7 @@ int run_host_roundtrip(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32
         d.bins_b_lo = b_lo;
         d.parity = *sc.parity;
         d.perm_lo = lo;
-        hipLaunchKernelGGL(dfn, dim3(grid), dim3(h->nwave * 64), 0, stream, d);
+        hipLaunchKernelGGL(rc_decide_kernel<4>, dim3(grid), dim3(h->nwave * 64), 0, stream, d);
         if (launch_ok() != RC_OK) return RC_E_DEVICE;
         ++launches;
         // the observation: 4 bytes to pinned host memory, then wait
@@ -2056,6 +2317,7 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
     h->ra.cdf_n = (h->ra.mode == RC_ROUTE_CDF) ? R - 1u : 0u;
     h->route_kind = h->ra.mode == RC_ROUTE_CDF ? RK_CDF : (h->ra.is_pow2 ? RK_POW2 : RK_MOD);
     h->ra.cdf_top = 0;
+    h->ra.mod_recip = R > 1u ? (uint32_t)((1ull << 32) / R) : 0u;
     while (h->ra.cdf_n && (h->ra.cdf_top << 1) <= h->ra.cdf_n && h->ra.cdf_top < (1u << 30))
         h->ra.cdf_top = h->ra.cdf_top ? h->ra.cdf_top << 1 : 1u;
 
@@ -2064,25 +2326,26 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
     h->full = h->wmax <= 16u || full_bytes <= full_image_limit;
     // Full image: [word-0 masks | CDF thresholds | guide] (the chain
     // section, everything the word-0 chain reads), then the mask rows, then
-    // the tool pairs.  Table image: the raw rows, then thresholds and guide.
+    // the tool pairs.  Table image: [route pairs | thresholds | guide], then
+    // the raw rows at a multiple of 16 words.
+    const uint32_t nb = (h->W + 15u) / 16u;
     const uint32_t row_words = h->full ? h->wmax : 16u;
     const uint32_t tab_words = (R + 1u) * (h->full ? row_words + 4u : row_words);
     auto pad4 = [](uint32_t x) { return (x + 3u) & ~3u; };
-    const uint32_t m0_words = h->full ? pad4(R + 1u) : 0u;
-    h->cdf_off = h->full ? m0_words : tab_words;
-    h->guide_off = h->cdf_off + pad4(h->ra.cdf_n);
-    const uint32_t after_guide = h->full ? tab_words + pad4(R) : 0u;  // rows and tools
-    // The chain kernel's LDS after the image: the count exchange ([16][nwave +
-    // 4] words; the table chain uses the first [2][nwave + 4]), then (full
-    // image, WMAX >= 16: the two-role or the pipelined split) the control
-    // handed to the replaying lanes, 16 steps of a 4-byte addend and a 4-byte
-    // control word per lane, then (full image) the effect stage of
-    // sub-wavefront bins, 4 + 16 bytes per lane.
-    h->nwave = h->full ? 4u : 8u;
-    const bool ctl_area = h->full && h->wmax >= 16u;
+    auto pad16 = [](uint32_t x) { return (x + 15u) & ~15u; };
+    const uint32_t m0_words = h->full ? pad4(R + 1u) : pad4(2u * R);
+    h->cdf_off = m0_words;
+    h->guide_off = h->cdf_off + (h->ra.cdf_n ? pad4(h->ra.cdf_n + CDF_PAD) : 0u);
+    const uint32_t after_guide = tab_words + (h->full ? pad4(R) : 12u);  // rows and tools (or the rows' alignment)
+    // The chain kernel's LDS after the image (full image): the count exchange
+    // ([16][nwave + 4] words), then (WMAX >= 16: the two-role or the
+    // pipelined split) the control handed to the replaying lanes, 16 steps of
+    // a 4-byte addend and a 4-byte control word per lane, then the effect
+    // stage of sub-wavefront bins, 4 + 16 bytes per lane.
+    const bool ctl_area = h->wmax >= 16u;
     const uint32_t na = h->nwave * 64u;
-    const size_t lds_after_image = 16u * (h->nwave + 4u) * 4u + (ctl_area ? 16u * na * 8u : 0u) +
-                                   (h->full ? na * 20u : 0u);
+    const size_t lds_after_image = h->full ? 16u * (h->nwave + 4u) * 4u + (ctl_area ? 16u * na * 8u : 0u) + na * 20u
+                                           : table_lds_after(nb);
     uint32_t guide_bits = 0, guide_n = 0;
     if (h->ra.mode == RC_ROUTE_CDF) {
         // Eight buckets per route, at most 2^12: with skewed routes the
@@ -2096,16 +2359,16 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
         auto lds_at = [&](uint32_t gb) {
             return ((size_t)h->guide_off + pad4((1u << gb) + 1u) + after_guide) * 4u + lds_after_image;
         };
-        if (lds_at(gmin) <= lds_two_per_cu)
-            while (guide_bits > gmin && lds_at(guide_bits) > lds_two_per_cu) --guide_bits;
+        const size_t lds_goal = lds_at(gmin) <= lds_two_per_cu ? lds_two_per_cu : h->lds_per_cu;
+        while (guide_bits > gmin && lds_at(guide_bits) > lds_goal) --guide_bits;
         guide_n = (1u << guide_bits) + 1u;
         h->ra.guide_shift = 32u - guide_bits;
     }
     const uint32_t guide_end = h->guide_off + pad4(guide_n);
-    h->chain_words = h->full ? guide_end : 0u;
-    h->rows_off = h->full ? guide_end : 0u;
+    h->chain_words = guide_end;
+    h->rows_off = h->full ? guide_end : pad16(guide_end);
     h->tools_off = h->rows_off + tab_words;
-    h->img_words = h->full ? h->tools_off + pad4(R) : guide_end;
+    h->img_words = h->full ? h->tools_off + pad4(R) : h->rows_off + tab_words;
     const size_t lds_image = (size_t)h->img_words * 4u;
     // chain_threads is the two-role (W >= 32) or one-lane workgroup; the
     // pipelined split launches three lanes per session.
@@ -2130,6 +2393,14 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
     if (rc == RC_OK && hipHostMalloc((void**)&h->h_word, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) rc = RC_E_NOMEM;
     if (rc == RC_OK && hipEventCreateWithFlags(&h->hrt_done, hipEventDisableTiming) != hipSuccess) rc = RC_E_DEVICE;
     if (rc == RC_OK) rc = noalloc_init(hip_device);
+    const size_t lanes = h->full ? 0u : (size_t)h->plan.n_bins * na;  // table image
+    if (rc == RC_OK && lanes && (hipMalloc((void**)&h->d_lane_s, lanes * sizeof(uint32_t)) != hipSuccess ||
+                                 hipMalloc((void**)&h->d_lane_i, lanes * sizeof(uint2)) != hipSuccess)) rc = RC_E_NOMEM;
+    if (rc == RC_OK && lanes) {
+        hipLaunchKernelGGL(rc_lanes_kernel, dim3(h->plan.n_bins), dim3(na), 0, 0, h->d_wdesc, h->d_offsets, h->C,
+                           h->d_lane_s, h->d_lane_i);
+        rc = launch_ok();
+    }
     if (rc == RC_OK) {
         ImageArgs ia;
         ia.raw = h->d_raw;
@@ -2151,6 +2422,7 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
         ia.rows_off = h->rows_off;
         hipLaunchKernelGGL(rc_prep_kernel, dim3((h->img_words + 255u) / 256u), dim3(256), 0, 0, ia);
         uint32_t span = 0;
+        // the copy waits for both kernels: callers' streams need not
         if (launch_ok() != RC_OK || hipMemcpy(&span, h->d_span, 4, hipMemcpyDeviceToHost) != hipSuccess)
             rc = RC_E_DEVICE;
         h->ra.guide_top = 0;
@@ -2159,10 +2431,16 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
     for (int v = 0; v < 4 && rc == RC_OK; ++v) {
         const bool fl = (v & 1) != 0, piped = (v & 2) != 0;
         if (piped && !has_piped(h->wmax, h->full)) continue;
-        ChainFn fn = pick_chain(h->wmax, h->exact, h->full, piped, h->route_kind, fl);
-        if (!fn) rc = RC_E_DEVICE;
-        if (rc == RC_OK && hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)h->chain_lds_bytes) != hipSuccess) rc = RC_E_DEVICE;
+        const void* fn = h->full ? (const void*)pick_chain(h->wmax, h->exact, piped, h->route_kind, fl)
+                                 : (const void*)pick_table(nb, h->route_kind, fl);
+        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)h->chain_lds_bytes) != hipSuccess)
+            rc = RC_E_DEVICE;
+        int per_cu = 0;
+        if (rc == RC_OK && !h->full && !fl) {
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 1024, h->chain_lds_bytes) != hipSuccess ||
+                per_cu < 1) rc = RC_E_DEVICE;
+            h->table_wgs = h->n_cu * (uint32_t)per_cu;
+        }
     }
     if (rc != RC_OK) {
         (void)hipGetLastError();
