@@ -1,17 +1,21 @@
-"""Build the HIP library ``librc_cohort.so`` (gfx950) in-tree with hipcc."""
+"""Build the HIP library ``librc_cohort.so`` (gfx950) in-tree with hipcc, and
+the binding's native caller ``_rc_call.so``."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SRC = os.path.join(PKG, "csrc", "rc_cohort.hip")
 SRC_HOST = [os.path.join(PKG, "csrc", "rc_host.cpp"),   # descriptor checks and launch plan
             os.path.join(PKG, "csrc", "rc_pack.cpp")]   # cohort shares and online compactor
+SRC_CALL = os.path.join(PKG, "csrc", "rc_call.c")          # CPython caller of the chain entry points
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "librc_cohort.so")
+CALL_LIB = os.path.join(PKG, "_rc_call.so")
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -40,7 +44,23 @@ def build(verbose: bool = False) -> str:
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
     os.replace(tmp, LIB)
+    build_call(verbose)
     return LIB
+
+
+def build_call(verbose: bool = False) -> str:
+    """Compile ``csrc/rc_call.c`` into ``_rc_call.so`` (host C, always)."""
+    cc = next((c for c in (shutil.which("cc"), shutil.which("gcc"), hipcc()) if c), None)
+    tmp = CALL_LIB + ".tmp%d" % os.getpid()
+    cmd = [cc, "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
+           "-I", INCLUDE, "-o", tmp, SRC_CALL]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("the compiler failed:\n" + res.stdout + res.stderr)
+    os.replace(tmp, CALL_LIB)
+    return CALL_LIB
 
 
 if __name__ == "__main__":

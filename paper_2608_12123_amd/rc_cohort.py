@@ -1,7 +1,8 @@
 """Thin Python binding of ``librc_cohort.so`` (the C ABI in include/rc_cohort.h).
 
-Argument marshalling only: every step of the transition runs in the HIP
-kernels.  There is no CPU fallback -- if the library is missing or no gfx950
+Argument marshalling only (ctypes; a small native module for the calls made
+once per launch): every step of the transition runs in the HIP kernels.
+There is no CPU fallback -- if the library is missing or no gfx950
 device is usable, the calls raise.
 
 The function names are those of the C ABI (``rc_cohort_create``,
@@ -99,11 +100,15 @@ class RcError(RuntimeError):
 
 
 _lib: Optional[ctypes.CDLL] = None
+# Set with _lib: the native caller of the two chain entry points (see
+# csrc/rc_call.c) and their addresses.
+_call = None
+_fn_run_chain = _fn_run_chain_noalloc = None
 
 
 def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     """Load the built HIP library.  Raises if it has not been built."""
-    global _lib
+    global _lib, _call, _fn_run_chain, _fn_run_chain_noalloc
     if _lib is not None:
         return _lib
     if not os.path.exists(path):
@@ -142,6 +147,15 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.rc_cohort_last_counts.restype = ctypes.c_int
     lib.rc_cohort_plan_info.argtypes = [ctypes.c_void_p, _P32, _P32, _P32]
     lib.rc_cohort_plan_info.restype = ctypes.c_int
+    try:
+        from . import _rc_call
+    except ImportError as e:
+        raise RuntimeError("_rc_call.so is not built (run paper_2608_12123_amd/build.py or "
+                           "__graft_entry__.build())") from e
+    _call = _rc_call.call
+    _fn_run_chain = ctypes.cast(lib.rc_cohort_run_chain, ctypes.c_void_p).value
+    if "rc_cohort_run_chain_noalloc" not in missing:
+        _fn_run_chain_noalloc = ctypes.cast(lib.rc_cohort_run_chain_noalloc, ctypes.c_void_p).value
     _lib = lib
     return lib
 
@@ -174,10 +188,25 @@ def _ptr(a: Optional[np.ndarray]):
     return None if a is None else a.ctypes.data_as(_P32)
 
 
+_torch_c = None  # torch's C module, once torch has initialised its device
+
+
+def _current_stream() -> int:
+    """The raw handle of torch's current stream on its current device (no
+    stream object is made: this runs once per launch)."""
+    global _torch_c
+    if _torch_c is None:
+        import torch
+        s = torch.cuda.current_stream().cuda_stream  # initialises the device
+        if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+            _torch_c = torch._C
+        return s
+    return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
+
+
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -222,10 +251,11 @@ def rc_cohort_step(h, buffers: RcBuffers, step: int, cohort_begin: int, cohort_e
 def rc_cohort_run_chain(h, buffers: RcBuffers, step0: int, n_steps: int, mode: int,
                         cohort_begin: int, cohort_end: int, stream=None,
                         check: bool = True) -> int:
-    st = load_library().rc_cohort_run_chain(h, ctypes.byref(buffers), step0 & 0xFFFFFFFF,
-                                            n_steps, mode, cohort_begin, cohort_end,
-                                            _stream_handle(stream))
-    if check:
+    if _call is None:
+        load_library()
+    st = _call(_fn_run_chain, h, buffers, step0, n_steps, mode, cohort_begin, cohort_end,
+               _stream_handle(stream))
+    if check and st != RC_OK:
         _check(st, "rc_cohort_run_chain")
     return st
 
@@ -235,9 +265,10 @@ def rc_cohort_run_chain_noalloc(h, buffers: RcBuffers, step0: int, n_steps: int,
                                 check: bool = True) -> int:
     """rc_cohort_run_chain with the host round trip's scratch in the
     library's fixed device array (no device allocation by the call)."""
-    st = load_library().rc_cohort_run_chain_noalloc(h, ctypes.byref(buffers), step0 & 0xFFFFFFFF,
-                                                    n_steps, mode, cohort_begin, cohort_end,
-                                                    _stream_handle(stream))
+    if _call is None:
+        load_library()
+    st = _call(_fn_run_chain_noalloc, h, buffers, step0, n_steps, mode, cohort_begin, cohort_end,
+               _stream_handle(stream))
     if check:
         _check(st, "rc_cohort_run_chain_noalloc")
     return st
