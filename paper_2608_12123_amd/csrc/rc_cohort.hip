@@ -192,7 +192,6 @@ struct RouteArgs {
     uint32_t mod_recip;   // floor(2^32 / R) when R is not
     uint32_t is_pow2;
     uint32_t cdf_n;       // R - 1 thresholds
-    uint32_t cdf_top;     // largest power of two <= cdf_n (0 if none)
     uint32_t guide_shift; // 32 - g (CDF mode)
     uint32_t guide_top;   // largest step of the search inside a guide bucket
 };
@@ -250,21 +249,6 @@ __device__ __forceinline__ uint32_t route_of(uint32_t o, const RouteArgs& ra,
     }
 }
 
-// Route key by a plain fixed-trip binary search over all thresholds (used by
-// the host-round-trip body kernel, which has no guide table).
-__device__ __forceinline__ uint32_t route_of_bsearch(uint32_t o, const RouteArgs& ra,
-                                                     const uint32_t* cdf) {
-    if (ra.mode == RC_ROUTE_MOD)
-        return ra.is_pow2 ? (o & ra.pow2_mask) : mod_routes(o, ra);
-    uint32_t pos = 0;
-    for (uint32_t stp = ra.cdf_top; stp != 0u; stp >>= 1) {
-        const uint32_t i = pos + stp;
-        const uint32_t v = cdf[(i <= ra.cdf_n ? i : ra.cdf_n) - 1u];
-        pos = (i <= ra.cdf_n && v <= o) ? i : pos;
-    }
-    return pos;
-}
-
 // Per-lane view of the plan for one bin.
 struct LaneCohort {
     uint32_t s;       // session
@@ -320,65 +304,6 @@ __device__ __forceinline__ LaneCohort lane_cohort(const uint32_t* __restrict__ w
         L.seg = below_hi & ~below_lo;
     }
     return L;
-}
-
-// Publish this wavefront's popcount (multi-wavefront cohorts), pass the
-// workgroup barrier, read the cohort's per-wavefront counts (cnt[wf .. wf+3];
-// only the first nw belong to the cohort).  Called only in workgroups that
-// hold a multi-wavefront cohort, the same number of times by every
-// wavefront.  Publication k goes to buffer k mod 2: its readers finish
-// before the barrier that follows publication k + 1, which precedes any
-// write of publication k + 2.
-__device__ __forceinline__ void publish_count(const LaneCohort& L, uint64_t bal, uint32_t lane,
-                                              uint32_t wv, uint32_t* cnt_lds, uint32_t cnt_stride,
-                                              uint32_t pub) {
-    if ((L.flags & WF_MULTI) && lane == 0u)
-        cnt_lds[(pub & 1u) * cnt_stride + wv] = (uint32_t)__popcll(bal);
-}
-
-__device__ __forceinline__ void barrier_read_counts(const LaneCohort& L, const uint32_t* cnt_lds,
-                                                    uint32_t cnt_stride, uint32_t& pub,
-                                                    uint32_t (&c4)[4]) {
-    __syncthreads();
-    if (L.flags & WF_MULTI) {
-        const uint32_t* buf = cnt_lds + (pub & 1u) * cnt_stride + (L.flags >> 24);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c4[i] = uni(buf[i]);
-    }
-    pub += 1u;
-}
-
-__device__ __forceinline__ void exchange_counts(const LaneCohort& L, uint64_t bal, uint32_t lane,
-                                                uint32_t wv, uint32_t* cnt_lds, uint32_t cnt_stride,
-                                                uint32_t& pub, uint32_t (&c4)[4]) {
-    publish_count(L, bal, lane, wv, cnt_lds, cnt_stride, pub);
-    barrier_read_counts(L, cnt_lds, cnt_stride, pub, c4);
-}
-
-// Stable-partition slot of this lane for a step with ballot `bal`; c4 holds
-// the cohort's per-wavefront counts of that step (multi-wavefront cohorts).
-__device__ __forceinline__ uint32_t slot_of(const LaneCohort& L, bool dk, uint64_t bal,
-                                            const uint32_t (&c4)[4], uint32_t& n1) {
-    uint32_t rank_t;
-    if (!(L.flags & WF_MULTI)) {
-        const uint64_t bs = bal & L.seg;
-        n1 = (uint32_t)__popcll(bs);
-        rank_t = lane_rank(bs);
-    } else {
-        const uint32_t wi = (L.flags >> 8) & 0xFFu;
-        const uint32_t nw = (L.flags >> 16) & 0xFFu;
-        uint32_t before = 0, total = 0;
-#pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) {
-            const uint32_t ci = uni(c4[i]);
-            total += (i < nw) ? ci : 0u;
-            before += (i < wi) ? ci : 0u;
-        }
-        n1 = total;
-        rank_t = before + lane_rank(bal);
-    }
-    const uint32_t in_c = L.s - L.b;
-    return L.b + (dk ? rank_t : n1 + (in_c - rank_t));
 }
 
 // ---------------------------------------------------------------------------
@@ -1660,111 +1585,168 @@ __global__ __launch_bounds__(1024, 4) void rc_table_kernel(TableArgs a) {
 // ---------------------------------------------------------------------------
 
 // Part 1: decide and compact one step.  Writes n_taken and, for every
-// stepped session, perm[slot] = sid | d << 31 (the stable partition of each
-// cohort, in effect order), and adds the workgroup's taken count to
-// ctr[parity] (the 4-byte word the host reads), one global atomic per
-// workgroup.  Block 0 clears the other parity's counter for the next step.
+// stepped session, where[s] = slot | d << 31 (its slot in the stable
+// partition of its cohort), and adds the workgroup's taken count to
+// ctr[parity] (the 4-byte word the host reads).  Block 0 clears the other
+// parity's counter for the next step.  A workgroup takes up to four bins at
+// a time, and there are at most DECIDE_WGS (see the launch): the adds to the one word are
+// performed one after the other, about 11 ns each (a workgroup and an add per
+// bin: 391 bins spent 4.3 us of 6.5 on them).
 struct DecideArgs {
     const uint32_t* state;
     const uint32_t* outcome;
     uint32_t* n_taken;
-    uint32_t* perm;           // slot j of the stepped range at perm[j - perm_lo]
+    uint32_t* where;          // session s of the stepped range at where[s - where_lo]
     uint32_t* ctr;            // [2]
     const uint32_t* offsets;
     const uint32_t* wdesc;
     uint32_t thr, step, t_index, n_cohorts, n_sessions;
     uint32_t cohort_begin, cohort_end;
-    uint32_t bins_a_lo, bins_a_n, bins_b_lo, parity, perm_lo;
+    uint32_t bins_a_lo, bins_a_n, bins_b_lo, n_units, parity, where_lo;
 };
 
-template <int NWAVE>
-__global__ __launch_bounds__(NWAVE * 64) void rc_decide_kernel(DecideArgs a) {
-    __shared__ uint32_t cnt_lds[2 * (NWAVE + 4)];
+constexpr uint32_t DECIDE_WGS = 256;
+
+__global__ __launch_bounds__(1024) void rc_decide_kernel(DecideArgs a) {
+    __shared__ uint32_t cnt[2][16 + 4];  // taken counts of the wavefronts (a cohort reads four from its first)
     __shared__ uint32_t wg_taken;
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = tid & 63u;
-    const uint32_t wv = tid >> 6;
+    const uint32_t wv = uni(tid >> 6);
+    const uint32_t per = blockDim.x / 256u;  // bins at a time
     if (tid == 0u) {
         wg_taken = 0u;
         if (blockIdx.x == 0u) a.ctr[a.parity ^ 1u] = 0u;
     }
-    const uint32_t i = blockIdx.x;
-    const uint32_t bin = i < a.bins_a_n ? a.bins_a_lo + i : a.bins_b_lo + (i - a.bins_a_n);
-    const LaneCohort L = lane_cohort(a.wdesc + ((size_t)bin * NWAVE + wv) * WD_WORDS,
-                                     a.offsets, lane, a.cohort_begin, a.cohort_end);
-    uint32_t s0w = 0, o = 0;
-    if (L.active) {
-        s0w = ld32(a.state, L.s << 2);
-        o = ld32(a.outcome, L.s << 2);
+    uint32_t taken = 0u, buf = 0u;
+    // the same trips for every wavefront: one barrier each
+    for (uint32_t u0 = blockIdx.x * per; u0 < a.n_units; u0 += gridDim.x * per, buf ^= 1u) {
+        const uint32_t u = u0 + (wv >> 2);
+        LaneCohort L{};
+        if (u < a.n_units) {
+            const uint32_t bin = u < a.bins_a_n ? a.bins_a_lo + u : a.bins_b_lo + (u - a.bins_a_n);
+            L = lane_cohort(a.wdesc + ((size_t)bin * 4u + (wv & 3u)) * WD_WORDS, a.offsets, lane, a.cohort_begin,
+                            a.cohort_end);
+        }
+        uint32_t s0w = 0, o = 0;
+        if (L.active) {
+            s0w = ld32(a.state, L.s << 2);
+            o = ld32(a.outcome, L.s << 2);
+        }
+        const bool dk = L.active && ((dev_fmix32(s0w ^ o ^ a.step) & 0xFFFFu) < a.thr);
+        const uint64_t bal = __ballot(dk);
+        if (lane == 0u) cnt[buf][wv] = (uint32_t)__popcll(bal);
+        __syncthreads();
+        uint32_t n1, rank_t;
+        if (!(L.flags & WF_MULTI)) {
+            const uint64_t bs = bal & L.seg;
+            n1 = (uint32_t)__popcll(bs);
+            rank_t = lane_rank(bs);
+        } else {
+            const uint32_t wi = (L.flags >> 8) & 0xFFu, nw = (L.flags >> 16) & 0xFFu;
+            const uint32_t* q = &cnt[buf][(wv & ~3u) + (L.flags >> 24)];
+            uint32_t before = 0;
+            n1 = 0;
+#pragma unroll
+            for (uint32_t i = 0; i < 4; ++i) {
+                const uint32_t ci = uni(q[i]);
+                n1 += (i < nw) ? ci : 0u;
+                before += (i < wi) ? ci : 0u;
+            }
+            rank_t = before + lane_rank(bal);
+        }
+        if (L.active) {
+            const uint32_t slot = L.b + (dk ? rank_t : n1 + ((L.s - L.b) - rank_t));
+            if (L.s == L.b) a.n_taken[(size_t)a.t_index * a.n_cohorts + L.c] = n1;
+            a.where[L.s - a.where_lo] = slot | (dk ? 0x80000000u : 0u);
+        }
+        taken += (uint32_t)__popcll(bal);
     }
-    const bool dk = L.active && ((dev_fmix32(s0w ^ o ^ a.step) & 0xFFFFu) < a.thr);
-    const uint64_t bal = __ballot(dk);
-    uint32_t c4[4] = {0u, 0u, 0u, 0u};
-    uint32_t pub = 0;
-    __syncthreads();  // wg_taken is cleared
-    if (L.flags & WF_WGMULTI) exchange_counts(L, bal, lane, wv, cnt_lds, NWAVE + 4, pub, c4);
-    uint32_t n1;
-    const uint32_t slot = slot_of(L, dk, bal, c4, n1);
-    if (L.active && L.s == L.b) a.n_taken[(size_t)a.t_index * a.n_cohorts + L.c] = n1;
-    if (L.active && slot - L.b < L.k) a.perm[slot - a.perm_lo] = L.s | (dk ? 0x80000000u : 0u);
-    if (lane == 0u && bal) atomicAdd(&wg_taken, (uint32_t)__popcll(bal));
+    if (lane == 0u && taken) atomicAdd(&wg_taken, taken);
     __syncthreads();
     if (tid == 0u && wg_taken) atomicAdd(&a.ctr[a.parity], wg_taken);
 }
 
-// Part 2: the route body the host selected.  Walks the slots [lo, hi) of
-// the stepped cohorts and handles the sessions of its own population, with
-// the slot the decide kernel assigned.
+// Part 2: the route body the host selected -- the taken one, the not-taken
+// one, or both in one launch when the step has sessions of both kinds.  One
+// lane per session, in session order: all state accesses are whole lines.
+// (A launch per body, each over the slots of both kinds, read and wrote the
+// lines that both kinds share twice: 100,000 sessions, W = 32, 7.4 + 6.8 us
+// a step against 6.0 for both at once, and 11 us between them.)
 struct BodyArgs {
     uint32_t* state;
     uint32_t* outcome;
     uint32_t* eff_sid;
     uint32_t* eff_tool;
     uint32_t* eff_payload;
-    const uint32_t* perm;  // slot j at perm[j - lo]
-    const uint32_t* raw;   // [R][16]
-    const uint32_t* cdf;
+    const uint32_t* where;  // session s at where[s - lo]
+    const uint32_t* raw;    // [R][16]
+    const uint32_t* cdf;    // thresholds and guide table of the handle's image
+    const uint32_t* guide;
     RouteArgs ra;
-    uint32_t ld, n_words, lo, hi, t_index, n_sessions;
+    uint32_t ld, n_words, lo, hi, t_index;
 };
 
-template <int WMAX, bool EXACT, bool TAKEN>
+enum : int { BODY_NOT = 0, BODY_TAKEN = 1, BODY_BOTH = 2 };
+
+template <int WMAX, bool EXACT, int BODY>
 __global__ __launch_bounds__(256) void rc_body_kernel(BodyArgs a) {
-    __shared__ uint32_t cdf_lds[RC_MAX_ROUTES];
-    const uint32_t tid = threadIdx.x;
-    if (a.ra.mode == RC_ROUTE_CDF) {
-        for (uint32_t i = tid; i < a.ra.cdf_n; i += 256u) cdf_lds[i] = a.cdf[i];
-        __syncthreads();
-    }
-    const uint32_t slot = a.lo + blockIdx.x * 256u + tid;
-    if (slot >= a.hi) return;
-    const uint32_t e = a.perm[slot - a.lo];
-    if ((e >> 31) != (TAKEN ? 1u : 0u)) return;
-    const uint32_t s = e & 0x7FFFFFFFu;
-    if (s >= a.n_sessions) return;  // never taken by a valid permutation
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= a.hi - a.lo) return;
+    const uint32_t e = a.where[i];
+    const bool dk = BODY == BODY_BOTH ? (e >> 31) != 0u : BODY == BODY_TAKEN;
+    const uint32_t slot = e & 0x7FFFFFFFu;
+    const uint32_t s = a.lo + i;
+    // never by what the decide kernel wrote: another kind, or a slot outside
+    // the stepped sessions
+    if (dk != ((e >> 31) != 0u) || slot - a.lo >= a.hi - a.lo) return;
     const uint32_t W = a.n_words;
     const uint32_t soff = s << 2;
     const uint32_t o = ld32(a.outcome, soff);
-    const uint32_t r = route_of_bsearch(o, a.ra, cdf_lds);
+    const uint32_t ld = opaque_s(a.ld);
     uint32_t S[WMAX];
 #pragma unroll
-    for (int w = 0; w < WMAX; ++w)
-        S[w] = (EXACT || (uint32_t)w < W) ? ld32(a.state + (size_t)w * a.ld, soff) : 0u;
-    if (TAKEN) {
-        const uint32_t* row = a.raw + r * 16u;
+    for (int w = 0; w < WMAX; w += 4) {
+        if (!EXACT && (uint32_t)w >= W) {
+            S[w] = S[w + 1] = S[w + 2] = S[w + 3] = 0u;
+            continue;
+        }
+        // in the last block, words past W repeat the last one: no branch between the loads
 #pragma unroll
-        for (int w = 0; w < WMAX; ++w) S[w] ^= row[w & 15] * (uint32_t)(w + 1);
-    } else {
+        for (int q = w; q < w + 4; ++q)
+            S[q] = ld32(a.state + (size_t)(EXACT || (uint32_t)q < W ? (uint32_t)q : W - 1u) * ld, soff);
+    }
+    const uint32_t r = a.ra.mode == RC_ROUTE_CDF ? route_of<RK_CDF>(o, a.ra, a.cdf, a.guide)
+                     : a.ra.is_pow2 ? route_of<RK_POW2>(o, a.ra, a.cdf, a.guide)
+                                    : route_of<RK_MOD>(o, a.ra, a.cdf, a.guide);
+    const uint32_t* row = a.raw + r * 16u;
+    const uint32_t tool = row[dk ? 1u : 0u] & 7u;
+    if constexpr (BODY == BODY_NOT) {
         const uint32_t sh = (31u - r) & 31u;
 #pragma unroll
         for (int w = 0; w < WMAX; ++w) S[w] = rotr32(S[w], sh) + o;
+    } else {
+        uint32_t m[WMAX < 16 ? WMAX : 16];
+#pragma unroll
+        for (int w = 0; w < (WMAX < 16 ? WMAX : 16); ++w) m[w] = 0u;
+        if (dk) {
+#pragma unroll
+            for (int w = 0; w < (WMAX < 16 ? WMAX : 16); w += 4) {
+                const uint4 v = *reinterpret_cast<const uint4*>(row + w);
+                m[w] = v.x; m[w + 1] = v.y; m[w + 2] = v.z; m[w + 3] = v.w;
+            }
+        }
+        const uint32_t sh = opaque(dk ? 0u : ((31u - r) & 31u));
+        const uint32_t oo = opaque(dk ? 0u : o);
+#pragma unroll
+        for (int w = 0; w < WMAX; ++w) S[w] = (rotr32(S[w], sh) ^ (m[w & 15] * (uint32_t)(w + 1))) + oo;
     }
 #pragma unroll
     for (int w = 0; w < WMAX; ++w)
-        if (EXACT || (uint32_t)w < W) st32(a.state + (size_t)w * a.ld, soff, S[w]);
+        if (EXACT || (uint32_t)w < W) st32(a.state + (size_t)w * ld, soff, S[w]);
     const size_t slice = (size_t)a.t_index * a.ld;
     st32(a.eff_sid + slice, slot << 2, s);
-    st32(a.eff_tool + slice, slot << 2, (a.raw[r * 16u + (TAKEN ? 1u : 0u)]) & 7u);
+    st32(a.eff_tool + slice, slot << 2, tool);
     st128(a.eff_payload + slice * 4u, slot << 4, make_uint4(S[0], S[1], S[2], S[3]));
     st32(a.outcome, soff, dev_fmix32(S[0]));
 }
@@ -1777,10 +1759,10 @@ __global__ __launch_bounds__(64) void rc_clear_kernel(uint32_t* p, uint32_t n) {
 }
 
 // Scratch of rc_cohort_run_chain_noalloc: two counter words, padding, then
-// the slot-to-session permutation of at most RC_NOALLOC_MAX_SESSIONS
+// the slots of at most RC_NOALLOC_MAX_SESSIONS
 // sessions.  Each device holds its own copy for the life of the process.
-constexpr uint32_t NOALLOC_PERM_OFF = 64u;
-__device__ __align__(256) uint32_t rc_noalloc_scratch[NOALLOC_PERM_OFF + RC_NOALLOC_MAX_SESSIONS];
+constexpr uint32_t NOALLOC_WHERE_OFF = 64u;
+__device__ __align__(256) uint32_t rc_noalloc_scratch[NOALLOC_WHERE_OFF + RC_NOALLOC_MAX_SESSIONS];
 
 // ---------------------------------------------------------------------------
 // Host side
@@ -1859,17 +1841,19 @@ bool use_piped(uint32_t wmax, bool full, int route_kind, uint32_t grid, uint32_t
 }
 
 template <int WMAX, bool EXACT>
-BodyFn body_fn(bool taken) {
-    return taken ? rc_body_kernel<WMAX, EXACT, true> : rc_body_kernel<WMAX, EXACT, false>;
+BodyFn body_fn(int body) {
+    return body == BODY_BOTH ? rc_body_kernel<WMAX, EXACT, BODY_BOTH>
+         : body == BODY_TAKEN ? rc_body_kernel<WMAX, EXACT, BODY_TAKEN>
+                              : rc_body_kernel<WMAX, EXACT, BODY_NOT>;
 }
 
-BodyFn pick_body(uint32_t wmax, bool exact, bool taken) {
+BodyFn pick_body(uint32_t wmax, bool exact, int body) {
     switch (wmax) {
-        case 4: return exact ? body_fn<4, true>(taken) : body_fn<4, false>(taken);
-        case 8: return exact ? body_fn<8, true>(taken) : body_fn<8, false>(taken);
-        case 16: return exact ? body_fn<16, true>(taken) : body_fn<16, false>(taken);
-        case 32: return exact ? body_fn<32, true>(taken) : body_fn<32, false>(taken);
-        default: return exact ? body_fn<64, true>(taken) : body_fn<64, false>(taken);
+        case 4: return exact ? body_fn<4, true>(body) : body_fn<4, false>(body);
+        case 8: return exact ? body_fn<8, true>(body) : body_fn<8, false>(body);
+        case 16: return exact ? body_fn<16, true>(body) : body_fn<16, false>(body);
+        case 32: return exact ? body_fn<32, true>(body) : body_fn<32, false>(body);
+        default: return exact ? body_fn<64, true>(body) : body_fn<64, false>(body);
     }
 }
 
@@ -1936,14 +1920,14 @@ struct rc_cohort {
     uint32_t* d_lane_s = nullptr;  // table image: plan lanes (see rc_lanes_kernel)
     uint2* d_lane_i = nullptr;
     uint32_t table_wgs = 256;      // table image: workgroups that fit the device at once
-    uint32_t* d_perm = nullptr;  // host round trip: [N] slot -> sid | d << 31
+    uint32_t* d_where = nullptr;  // host round trip: [N] slot -> sid | d << 31
     uint32_t* d_ctr = nullptr;
     uint32_t* h_word = nullptr;  // pinned
     uint32_t parity = 0;
     bool ctr_dirty = false;
     uint32_t last_launches = 0, last_d2h = 0;
     // Recorded after the last body kernel of a host-round-trip call; the next
-    // such call's stream waits for it before touching d_perm / d_ctr.
+    // such call's stream waits for it before touching d_where / d_ctr.
     hipEvent_t hrt_done = nullptr;
     bool hrt_pending = false;
     uint32_t n_cu = 256;             // compute units of the device
@@ -1966,7 +1950,7 @@ void free_handle(rc_cohort* h) {
         (void)hipFree(h->d_wdesc);
         (void)hipFree(h->d_lane_s);
         (void)hipFree(h->d_lane_i);
-        (void)hipFree(h->d_perm);
+        (void)hipFree(h->d_where);
         (void)hipFree(h->d_ctr);
         if (h->h_word) (void)hipHostFree(h->h_word);
         if (h->hrt_done) (void)hipEventDestroy(h->hrt_done);
@@ -2157,12 +2141,11 @@ int run_resident(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32_t T,
     return RC_OK;
 }
 
-// Where a host-round-trip call keeps its per-step scratch: the
-// slot-to-session permutation of the stepped range (slot j at
-// perm[j - lo]) and the two counter words of the 4-byte observation, plus
+// Where a host-round-trip call keeps its per-step scratch: the slot of
+// every stepped session (session s at where[s - lo]) and the two counter words of the 4-byte observation, plus
 // the event that orders the calls sharing them.
 struct HrtScratch {
-    uint32_t* perm;
+    uint32_t* where;
     uint32_t* ctr;
     uint32_t* parity;   // which counter word the next step adds to
     hipEvent_t done;    // recorded after a call's last body kernel
@@ -2184,19 +2167,24 @@ int run_host_roundtrip(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32
     }
     uint32_t a_lo, a_n, b_lo, b_n;
     bins_of_range(h->plan, cb, ce, a_lo, a_n, b_lo, b_n);
-    const uint32_t grid = a_n + b_n;
+    const uint32_t units = a_n + b_n;
+    // Few workgroups, for their adds to the one counter -- unless hardly any
+    // bin has a taken session (under one in four), so that hardly any adds:
+    // then a workgroup per bin.  100,000 sessions, 391 bins, 8 steps: 202 /
+    // 190 / 183 us with 1 / 2 / 4 bins at p = 0.5, 163 / 168 / 171 us at p = 0.
+    const bool adds = h->thr >= 64u;
+    const uint32_t per = !adds ? 1u : units < 4u ? units : 4u, wgs = (units + per - 1u) / per;
+    const uint32_t grid = adds && wgs > DECIDE_WGS ? DECIDE_WGS : wgs;
     const uint32_t lo = h->offsets[cb], hi = h->offsets[ce];
     const uint32_t n_range = hi - lo;
     const uint32_t body_grid = (n_range + 255u) / 256u;
-    BodyFn taken_fn = pick_body(h->wmax, h->exact, true);
-    BodyFn not_fn = pick_body(h->wmax, h->exact, false);
     for (uint32_t t = 0; t < T; ++t) {
         if (!sc.clear_first) h->ctr_dirty = true;  // the handle's counters; cleared again when the step completes
         DecideArgs d;
         d.state = b->state;
         d.outcome = b->outcome;
         d.n_taken = b->n_taken;
-        d.perm = sc.perm;
+        d.where = sc.where;
         d.ctr = sc.ctr;
         d.offsets = h->d_offsets;
         d.wdesc = h->d_wdesc;
@@ -2210,9 +2198,10 @@ int run_host_roundtrip(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32
         d.bins_a_lo = a_lo;
         d.bins_a_n = a_n;
         d.bins_b_lo = b_lo;
+        d.n_units = units;
         d.parity = *sc.parity;
-        d.perm_lo = lo;
-        hipLaunchKernelGGL(rc_decide_kernel<4>, dim3(grid), dim3(h->nwave * 64), 0, stream, d);
+        d.where_lo = lo;
+        hipLaunchKernelGGL(rc_decide_kernel, dim3(grid), dim3(per * 256u), 0, stream, d);
         if (launch_ok() != RC_OK) return RC_E_DEVICE;
         ++launches;
         // the observation: 4 bytes to pinned host memory, then wait
@@ -2222,33 +2211,27 @@ int run_host_roundtrip(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32
         if (hipStreamSynchronize(stream) != hipSuccess) return RC_E_DEVICE;
         const uint32_t n_taken_total = *h->h_word;
         if (n_taken_total > n_range) return RC_E_DEVICE;
-        // the host branch: launch the selected route body (or both)
+        // the host branch: launch the selected route body, or both in one
         BodyArgs ba;
         ba.state = b->state;
         ba.outcome = b->outcome;
         ba.eff_sid = b->eff_sid;
         ba.eff_tool = b->eff_tool;
         ba.eff_payload = b->eff_payload;
-        ba.perm = sc.perm;
+        ba.where = sc.where;
         ba.raw = h->d_raw;
-        ba.cdf = h->d_cdf;
+        ba.cdf = h->d_img + h->cdf_off;
+        ba.guide = h->d_img + h->guide_off;
         ba.ra = h->ra;
         ba.ld = b->ld;
         ba.n_words = h->W;
         ba.lo = lo;
         ba.hi = hi;
         ba.t_index = t;
-        ba.n_sessions = h->N;
-        if (n_taken_total > 0u) {
-            hipLaunchKernelGGL(taken_fn, dim3(body_grid), dim3(256), 0, stream, ba);
-            if (launch_ok() != RC_OK) return RC_E_DEVICE;
-            ++launches;
-        }
-        if (n_taken_total < n_range) {
-            hipLaunchKernelGGL(not_fn, dim3(body_grid), dim3(256), 0, stream, ba);
-            if (launch_ok() != RC_OK) return RC_E_DEVICE;
-            ++launches;
-        }
+        const int body = n_taken_total == 0u ? BODY_NOT : n_taken_total == n_range ? BODY_TAKEN : BODY_BOTH;
+        hipLaunchKernelGGL(pick_body(h->wmax, h->exact, body), dim3(body_grid), dim3(256), 0, stream, ba);
+        if (launch_ok() != RC_OK) return RC_E_DEVICE;
+        ++launches;
         *sc.parity ^= 1u;
         if (!sc.clear_first) h->ctr_dirty = false;
     }
@@ -2259,7 +2242,7 @@ int run_host_roundtrip(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32
     return RC_OK;
 }
 
-// The handle's own scratch (d_perm, d_ctr), after restoring cleared counters
+// The handle's own scratch (d_where, d_ctr), after restoring cleared counters
 // if a previous call stopped inside a step.
 int run_host_roundtrip_handle(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32_t T,
                               uint32_t cb, uint32_t ce, hipStream_t stream) {
@@ -2269,7 +2252,7 @@ int run_host_roundtrip_handle(rc_cohort* h, const rc_buffers* b, uint32_t step0,
         h->parity = 0;
         h->ctr_dirty = false;
     }
-    HrtScratch sc{h->d_perm + h->offsets[cb], h->d_ctr, &h->parity, h->hrt_done, &h->hrt_pending, false};
+    HrtScratch sc{h->d_where + h->offsets[cb], h->d_ctr, &h->parity, h->hrt_done, &h->hrt_pending, false};
     return run_host_roundtrip(h, b, step0, T, cb, ce, stream, sc);
 }
 
@@ -2316,10 +2299,7 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
     h->ra.pow2_mask = h->ra.is_pow2 ? R - 1u : 0u;
     h->ra.cdf_n = (h->ra.mode == RC_ROUTE_CDF) ? R - 1u : 0u;
     h->route_kind = h->ra.mode == RC_ROUTE_CDF ? RK_CDF : (h->ra.is_pow2 ? RK_POW2 : RK_MOD);
-    h->ra.cdf_top = 0;
     h->ra.mod_recip = R > 1u ? (uint32_t)((1ull << 32) / R) : 0u;
-    while (h->ra.cdf_n && (h->ra.cdf_top << 1) <= h->ra.cdf_n && h->ra.cdf_top < (1u << 30))
-        h->ra.cdf_top = h->ra.cdf_top ? h->ra.cdf_top << 1 : 1u;
 
     // table image layout (see the file comment)
     const size_t full_bytes = (size_t)(R + 1u) * (h->wmax + 4u) * 4u;
@@ -2387,7 +2367,7 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
     if (rc == RC_OK && hipMalloc((void**)&h->d_span, 16) != hipSuccess) rc = RC_E_NOMEM;
     if (rc == RC_OK && hipMemset(h->d_span, 0, 16) != hipSuccess) rc = RC_E_DEVICE;
     if (rc == RC_OK) rc = dev_upload(&h->d_wdesc, h->plan.wdesc.data(), h->plan.wdesc.size() * 4u);
-    if (rc == RC_OK && hipMalloc((void**)&h->d_perm, (size_t)h->N * sizeof(uint32_t)) != hipSuccess) rc = RC_E_NOMEM;
+    if (rc == RC_OK && hipMalloc((void**)&h->d_where, (size_t)h->N * sizeof(uint32_t)) != hipSuccess) rc = RC_E_NOMEM;
     if (rc == RC_OK && hipMalloc((void**)&h->d_ctr, 2 * sizeof(uint32_t)) != hipSuccess) rc = RC_E_NOMEM;
     if (rc == RC_OK && hipMemset(h->d_ctr, 0, 2 * sizeof(uint32_t)) != hipSuccess) rc = RC_E_DEVICE;
     if (rc == RC_OK && hipHostMalloc((void**)&h->h_word, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) rc = RC_E_NOMEM;
@@ -2487,7 +2467,7 @@ int rc_cohort_run_chain_noalloc(rc_cohort* h, const rc_buffers* b, uint32_t step
     uint32_t* base = g_noalloc_ptr[h->device];  // resolved by rc_cohort_create
     if (!base) return RC_E_DEVICE;
     uint32_t parity = 0;
-    HrtScratch sc{base + NOALLOC_PERM_OFF, base, &parity, g_noalloc_done[h->device],
+    HrtScratch sc{base + NOALLOC_WHERE_OFF, base, &parity, g_noalloc_done[h->device],
                   &g_noalloc_pending[h->device], true};
     return run_host_roundtrip(h, b, step0, n_steps, cohort_begin, cohort_end, stream, sc);
 }
