@@ -4,8 +4,8 @@
 // Kernels
 //   rc_prep_kernel    once per handle: builds the route-table image that every
 //                     workgroup stages into LDS.
-//   rc_lanes_kernel   once per handle (table image): what every plan lane
-//                     needs to know of its session and cohort.
+//   rc_lanes_kernel   once per handle: what every plan lane needs to know of
+//                     its session and cohort.
 //   rc_chain_kernel, rc_table_kernel
 //                     device-resident chain (Section 7 "Device resident"),
 //                     with the full or the table image: one launch runs T
@@ -30,7 +30,7 @@
 // workgroup of 4 wavefronts of plan lanes.  A cohort of at most 64 sessions never
 // straddles a wavefront; a larger one starts on a wavefront boundary and spans
 // whole wavefronts; no cohort straddles a bin.  Each wavefront has a 64-byte
-// descriptor read with scalar loads.  The compaction
+// descriptor, from which rc_lanes_kernel makes a 12-byte record per lane.  The compaction
 // (stable partition, taken first) is a wavefront ballot + mbcnt rank; a
 // cohort spanning wavefronts adds an LDS exchange of per-wavefront popcounts
 // behind one workgroup barrier per chunk of steps.
@@ -306,6 +306,80 @@ __device__ __forceinline__ LaneCohort lane_cohort(const uint32_t* __restrict__ w
     return L;
 }
 
+// Per lane of the plan, built once per handle: the session (TS_IDLE: no
+// session), and what the compaction needs of its cohort.
+constexpr uint32_t TS_IDLE = 0xFFFFFFFFu;
+enum : uint32_t {
+    TI_INC = 0,      // bits 0..7: index of the session in its cohort
+    TI_SIZE = 8,     // bits 8..16: cohort size
+    TI_LO = 17,      // bits 17..22: first lane of the cohort (sub-wavefront cohorts)
+    TI_MULTI = 23,   // bit 23: the wavefront is part of a cohort of > 64 sessions, and of it:
+    TI_WI = 24,      // bits 24..25: this wavefront's index in the cohort
+    TI_NW = 26,      // bits 26..27: wavefronts of the cohort, minus one
+    TI_FIRST = 28    // bits 28..29: first wavefront in the workgroup
+};
+
+__global__ __launch_bounds__(256) void rc_lanes_kernel(const uint32_t* wdesc, const uint32_t* offsets,
+                                                       uint32_t n_cohorts, uint32_t* lane_s, uint2* lane_i) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = blockIdx.x * 4u + (threadIdx.x >> 6);
+    const LaneCohort L = lane_cohort(wdesc + (size_t)wave * WD_WORDS, offsets, lane, 0u, n_cohorts);
+    uint32_t v = 0u;
+    if (L.flags & WF_MULTI)
+        v = (1u << TI_MULTI) | (((L.flags >> 8) & 3u) << TI_WI) | ((((L.flags >> 16) - 1u) & 3u) << TI_NW) |
+            (((L.flags >> 24) & 3u) << TI_FIRST);
+    if (L.active) {
+        const uint32_t in_c = L.s - L.b;
+        v |= in_c | (L.k << TI_SIZE);
+        if (!(L.flags & WF_MULTI)) v |= (lane - in_c) << TI_LO;
+    }
+    lane_s[(size_t)wave * 64u + lane] = L.active ? L.s : TS_IDLE;
+    lane_i[(size_t)wave * 64u + lane] = make_uint2(L.active ? L.c : 0u, v);
+}
+
+// A lane's view of the plan from its record: the same fields as lane_cohort,
+// without walking the wavefront's cohorts (scalar loads that wait for one
+// another: a wavefront of eight small cohorts spent 1.2 us on them).
+__device__ __forceinline__ LaneCohort lane_record(const uint32_t* __restrict__ lane_s,
+                                                  const uint2* __restrict__ lane_i, size_t at, uint32_t s_lo,
+                                                  uint32_t s_n) {
+    const uint32_t s = lane_s[at];
+    const uint2 i = lane_i[at];
+    LaneCohort L;
+    L.s = s;
+    L.c = i.x;
+    L.b = s - (i.y & 255u);
+    L.k = (i.y >> TI_SIZE) & 511u;
+    const uint32_t fl = uni(i.y);  // the same in every lane of the wavefront
+    const uint32_t wi = (fl >> TI_WI) & 3u, nw = ((fl >> TI_NW) & 3u) + 1u, first = (fl >> TI_FIRST) & 3u;
+    const bool multi = (fl >> TI_MULTI) & 1u;
+    L.flags = multi ? (uint32_t)WF_MULTI | (wi << 8) | (nw << 16) | (first << 24) : 0u;
+    L.active = s - s_lo < s_n;  // TS_IDLE is past every session
+    const uint32_t lo = (i.y >> TI_LO) & 63u, hi = lo + L.k;
+    L.seg = multi ? 0ull : (hi >= 64u ? ~0ull : ((1ull << hi) - 1ull)) & ~((1ull << lo) - 1ull);
+    return L;
+}
+
+// The same from the wavefront's descriptor where one cohort has the whole
+// wavefront (a scalar load, the shorter latency: one 256-session cohort, T =
+// 7, 4.31 us against 4.47 from the record), else from the record.
+template <bool MULTI>
+__device__ __forceinline__ LaneCohort lane_view(const uint32_t* __restrict__ wd, const uint32_t* __restrict__ lane_s,
+                                                const uint2* __restrict__ lane_i, size_t at, uint32_t lane,
+                                                uint32_t s_lo, uint32_t s_n) {
+    if (!MULTI && uni(wd[WD_NCOH]) > 1u) return lane_record(lane_s, lane_i, at, s_lo, s_n);
+    LaneCohort L;
+    L.s = uni(wd[WD_S0]) + lane;
+    L.c = uni(wd[WD_CFIRST]);
+    L.b = uni(wd[WD_BFIRST]);
+    L.k = uni(wd[WD_KFIRST]);
+    L.flags = uni(wd[WD_FLAGS]);
+    L.active = lane < uni(wd[WD_NACT]) && L.s - s_lo < s_n;
+    // a sub-wavefront cohort's lanes start at lane 0
+    L.seg = MULTI ? 0ull : L.k >= 64u ? ~0ull : ((1ull << L.k) - 1ull);
+    return L;
+}
+
 // ---------------------------------------------------------------------------
 // Table image (built once per handle)
 // ---------------------------------------------------------------------------
@@ -393,11 +467,12 @@ struct ChainArgs {
     uint32_t* eff_payload;
     uint32_t* n_taken;
     const uint32_t* img;      // LDS image, img_words words
-    const uint32_t* offsets;  // [C+1]
     const uint32_t* wdesc;    // [bins][waves][WD_WORDS]
+    const uint32_t* lane_s;   // [bins][256] (see rc_lanes_kernel)
+    const uint2* lane_i;
     RouteArgs ra;
     uint32_t ld, n_words, n_cohorts, thr, step0, n_steps;
-    uint32_t cohort_begin, cohort_end;
+    uint32_t s_lo, s_n;       // sessions of the stepped cohorts: [s_lo, s_lo + s_n)
     uint32_t bins_a_lo, bins_a_n, bins_b_lo, bins_b_n;  // sub-wave / multi-wave bins
     uint32_t img_words, tools_off, cdf_off, guide_off;  // in words
     uint32_t rows_off;     // full image: first word of the mask rows
@@ -540,8 +615,16 @@ struct ChainF {
         const uint32_t* lds_tools = lds + a.tools_off;
 
         const uint32_t rows_b = a.rows_off * 4u;  // byte offset of the mask rows in LDS
-        const LaneCohort L = lane_cohort(a.wdesc + ((size_t)bin * NWAVE + wa) * WD_WORDS,
-                                         a.offsets, lane, a.cohort_begin, a.cohort_end);
+        LaneCohort L;
+        // One lane per session at W <= 8 keeps little else in flight while it
+        // waits, and takes the record throughout: 200,000 sessions in ragged
+        // cohorts, W = 8, T = 4, 12.9 us with lane_view, 10.8 without; at W =
+        // 16, T = 4, 300,000 sessions in 256-session cohorts 15.0 and 15.5.
+        if constexpr (SPLIT || (MULTI && WMAX >= 16))
+            L = lane_view<MULTI>(a.wdesc + ((size_t)bin * NWAVE + wa) * WD_WORDS, a.lane_s, a.lane_i,
+                          (size_t)bin * NLA + alane, lane, a.s_lo, a.s_n);
+        else
+            L = lane_record(a.lane_s, a.lane_i, (size_t)bin * NLA + alane, a.s_lo, a.s_n);
         const uint32_t soff = L.s << 2;
         typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
         const u32x4* src = reinterpret_cast<const u32x4*>(a.img);
@@ -1099,37 +1182,6 @@ void rc_chain_kernel(ChainArgs a) {
 // ---------------------------------------------------------------------------
 // Device-resident chain, table image
 // ---------------------------------------------------------------------------
-// Per lane of the plan, built once per handle: the session (TS_IDLE: no
-// session), and what the compaction needs of its cohort.
-constexpr uint32_t TS_IDLE = 0xFFFFFFFFu;
-enum : uint32_t {
-    TI_INC = 0,      // bits 0..7: index of the session in its cohort
-    TI_SIZE = 8,     // bits 8..16: cohort size
-    TI_LO = 17,      // bits 17..22: first lane of the cohort (sub-wavefront cohorts)
-    TI_MULTI = 23,   // bit 23: the wavefront is part of a cohort of > 64 sessions, and of it:
-    TI_WI = 24,      // bits 24..25: this wavefront's index in the cohort
-    TI_NW = 26,      // bits 26..27: wavefronts of the cohort, minus one
-    TI_FIRST = 28    // bits 28..29: first wavefront in the workgroup
-};
-
-__global__ __launch_bounds__(256) void rc_lanes_kernel(const uint32_t* wdesc, const uint32_t* offsets,
-                                                       uint32_t n_cohorts, uint32_t* lane_s, uint2* lane_i) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = blockIdx.x * 4u + (threadIdx.x >> 6);
-    const LaneCohort L = lane_cohort(wdesc + (size_t)wave * WD_WORDS, offsets, lane, 0u, n_cohorts);
-    uint32_t v = 0u;
-    if (L.flags & WF_MULTI)
-        v = (1u << TI_MULTI) | (((L.flags >> 8) & 3u) << TI_WI) | ((((L.flags >> 16) - 1u) & 3u) << TI_NW) |
-            (((L.flags >> 24) & 3u) << TI_FIRST);
-    if (L.active) {
-        const uint32_t in_c = L.s - L.b;
-        v |= in_c | (L.k << TI_SIZE);
-        if (!(L.flags & WF_MULTI)) v |= (lane - in_c) << TI_LO;
-    }
-    lane_s[(size_t)wave * 64u + lane] = L.active ? L.s : TS_IDLE;
-    lane_i[(size_t)wave * 64u + lane] = make_uint2(L.active ? L.c : 0u, v);
-}
-
 struct TableArgs {
     uint32_t* state;
     uint32_t* outcome;
@@ -1598,10 +1650,10 @@ struct DecideArgs {
     uint32_t* n_taken;
     uint32_t* where;          // session s of the stepped range at where[s - where_lo]
     uint32_t* ctr;            // [2]
-    const uint32_t* offsets;
-    const uint32_t* wdesc;
+    const uint32_t* lane_s;   // [bins][256] (see rc_lanes_kernel)
+    const uint2* lane_i;
     uint32_t thr, step, t_index, n_cohorts, n_sessions;
-    uint32_t cohort_begin, cohort_end;
+    uint32_t s_n;             // stepped sessions, from where_lo
     uint32_t bins_a_lo, bins_a_n, bins_b_lo, n_units, parity, where_lo;
 };
 
@@ -1625,8 +1677,7 @@ __global__ __launch_bounds__(1024) void rc_decide_kernel(DecideArgs a) {
         LaneCohort L{};
         if (u < a.n_units) {
             const uint32_t bin = u < a.bins_a_n ? a.bins_a_lo + u : a.bins_b_lo + (u - a.bins_a_n);
-            L = lane_cohort(a.wdesc + ((size_t)bin * 4u + (wv & 3u)) * WD_WORDS, a.offsets, lane, a.cohort_begin,
-                            a.cohort_end);
+            L = lane_record(a.lane_s, a.lane_i, (size_t)bin * 256u + (tid & 255u), a.where_lo, a.s_n);
         }
         uint32_t s0w = 0, o = 0;
         if (L.active) {
@@ -1917,8 +1968,8 @@ struct rc_cohort {
     uint32_t* d_img = nullptr;
     uint32_t* d_span = nullptr;
     uint32_t* d_wdesc = nullptr;
-    uint32_t* d_lane_s = nullptr;  // table image: plan lanes (see rc_lanes_kernel)
-    uint2* d_lane_i = nullptr;
+    uint2* d_lane_i = nullptr;     // plan lanes (see rc_lanes_kernel)
+    uint32_t* d_lane_s = nullptr;  // in the same allocation
     uint32_t table_wgs = 256;      // table image: workgroups that fit the device at once
     uint32_t* d_where = nullptr;  // host round trip: [N] slot -> sid | d << 31
     uint32_t* d_ctr = nullptr;
@@ -1948,7 +1999,6 @@ void free_handle(rc_cohort* h) {
         (void)hipFree(h->d_img);
         (void)hipFree(h->d_span);
         (void)hipFree(h->d_wdesc);
-        (void)hipFree(h->d_lane_s);
         (void)hipFree(h->d_lane_i);
         (void)hipFree(h->d_where);
         (void)hipFree(h->d_ctr);
@@ -2109,8 +2159,9 @@ int run_resident(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32_t T,
     a.eff_payload = b->eff_payload;
     a.n_taken = b->n_taken;
     a.img = h->d_img;
-    a.offsets = h->d_offsets;
     a.wdesc = h->d_wdesc;
+    a.lane_s = h->d_lane_s;
+    a.lane_i = h->d_lane_i;
     a.ra = h->ra;
     a.ld = b->ld;
     a.n_words = h->W;
@@ -2118,8 +2169,8 @@ int run_resident(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32_t T,
     a.thr = h->thr;
     a.step0 = step0;
     a.n_steps = T;
-    a.cohort_begin = cb;
-    a.cohort_end = ce;
+    a.s_lo = h->offsets[cb];
+    a.s_n = h->offsets[ce] - a.s_lo;
     bins_of_range(h->plan, cb, ce, a.bins_a_lo, a.bins_a_n, a.bins_b_lo, a.bins_b_n);
     a.img_words = h->img_words;
     a.tools_off = h->tools_off;
@@ -2186,15 +2237,14 @@ int run_host_roundtrip(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32
         d.n_taken = b->n_taken;
         d.where = sc.where;
         d.ctr = sc.ctr;
-        d.offsets = h->d_offsets;
-        d.wdesc = h->d_wdesc;
+        d.lane_s = h->d_lane_s;
+        d.lane_i = h->d_lane_i;
         d.thr = h->thr;
         d.step = step0 + t;
         d.t_index = t;
         d.n_cohorts = h->C;
         d.n_sessions = h->N;
-        d.cohort_begin = cb;
-        d.cohort_end = ce;
+        d.s_n = n_range;
         d.bins_a_lo = a_lo;
         d.bins_a_n = a_n;
         d.bins_b_lo = b_lo;
@@ -2373,10 +2423,12 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
     if (rc == RC_OK && hipHostMalloc((void**)&h->h_word, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) rc = RC_E_NOMEM;
     if (rc == RC_OK && hipEventCreateWithFlags(&h->hrt_done, hipEventDisableTiming) != hipSuccess) rc = RC_E_DEVICE;
     if (rc == RC_OK) rc = noalloc_init(hip_device);
-    const size_t lanes = h->full ? 0u : (size_t)h->plan.n_bins * na;  // table image
-    if (rc == RC_OK && lanes && (hipMalloc((void**)&h->d_lane_s, lanes * sizeof(uint32_t)) != hipSuccess ||
-                                 hipMalloc((void**)&h->d_lane_i, lanes * sizeof(uint2)) != hipSuccess)) rc = RC_E_NOMEM;
-    if (rc == RC_OK && lanes) {
+    // plan lanes: 8 bytes each, then 4 bytes each
+    const size_t lanes = (size_t)h->plan.n_bins * na;
+    if (rc == RC_OK && hipMalloc((void**)&h->d_lane_i, lanes * (sizeof(uint2) + sizeof(uint32_t))) != hipSuccess)
+        rc = RC_E_NOMEM;
+    if (rc == RC_OK) {
+        h->d_lane_s = reinterpret_cast<uint32_t*>(h->d_lane_i + lanes);
         hipLaunchKernelGGL(rc_lanes_kernel, dim3(h->plan.n_bins), dim3(na), 0, 0, h->d_wdesc, h->d_offsets, h->C,
                            h->d_lane_s, h->d_lane_i);
         rc = launch_ok();
