@@ -773,7 +773,8 @@ def roofline_of(key, inp, T, k_avg_ms):
     traffic = stored_traffic(key)
     blk = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-           "kernel": "rc_chain_kernel", "algorithmic_bytes_per_launch": abytes,
+           "kernel": "rc_table_kernel" if key == "s1m" else "rc_chain_kernel",
+           "algorithmic_bytes_per_launch": abytes,
            "kernel_us": round(k_avg_ms * 1e3, 3)}
     if traffic is not None:
         blk["traffic_over_algorithmic"] = round(traffic / abytes, 4)
@@ -876,7 +877,7 @@ def summarize_trace(trace_dir, plan_path):
         for line in f:
             if line.startswith("{") and "trace_blocks" in line:
                 plan = json.loads(line)
-    lib_kernels = ("rc_chain_kernel", "rc_decide_kernel", "rc_body_kernel", "rc_clear_kernel")
+    lib_kernels = ("rc_chain_kernel", "rc_table_kernel", "rc_decide_kernel", "rc_body_kernel", "rc_clear_kernel")
     ev, blit = [], []
     for r in rows("*kernel_trace.csv"):
         name = r.get("Kernel_Name", "")
@@ -908,7 +909,7 @@ def summarize_trace(trace_dir, plan_path):
         n = b["invocations"]
         lo, hi = seg["start"] - gap_ns / 2, seg["end"] + gap_ns / 4
         inside = lambda ts: sum(1 for t in ts if lo <= t <= hi) / n
-        chain = [e[1] - e[0] for e in seg["ev"] if "rc_chain_kernel" in e[2]]
+        chain = [e[1] - e[0] for e in seg["ev"] if "rc_chain_kernel" in e[2] or "rc_table_kernel" in e[2]]
         lines.append("| %s | %s | %d | %.2f | %.2f | %.2f | %.2f | %s | %s |" % (
             b["workload"], b["mechanism"], n, len(seg["ev"]) / n, inside(blit), inside(api),
             inside(sdma), tuple(b["library_counts_per_invocation"]),
