@@ -1,11 +1,14 @@
 """Build the HIP library ``librc_cohort.so`` (gfx950) in-tree with hipcc, and
-the binding's native caller ``_rc_call.so``."""
+the binding's native caller ``_rc_call`` where the interpreter's headers and a
+C compiler are there."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
 import sysconfig
+import warnings
+from typing import Optional
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -15,7 +18,8 @@ SRC_HOST = [os.path.join(PKG, "csrc", "rc_host.cpp"),   # descriptor checks and 
 SRC_CALL = os.path.join(PKG, "csrc", "rc_call.c")          # CPython caller of the chain entry points
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "librc_cohort.so")
-CALL_LIB = os.path.join(PKG, "_rc_call.so")
+# named for the interpreter it is built for, so that another one does not load it
+CALL_LIB = os.path.join(PKG, "_rc_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -48,17 +52,27 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
-def build_call(verbose: bool = False) -> str:
-    """Compile ``csrc/rc_call.c`` into ``_rc_call.so`` (host C, always)."""
+def build_call(verbose: bool = False) -> Optional[str]:
+    """Compile ``csrc/rc_call.c`` into the extension module ``_rc_call`` (host
+    C, always).  Where that is not possible (no C compiler, no Python headers)
+    this warns and returns None: the binding then marshals with ctypes."""
+    for old in (CALL_LIB, os.path.join(PKG, "_rc_call.so")):  # never one of other sources
+        if os.path.exists(old):
+            os.remove(old)
     cc = next((c for c in (shutil.which("cc"), shutil.which("gcc"), hipcc()) if c), None)
     tmp = CALL_LIB + ".tmp%d" % os.getpid()
     cmd = [cc, "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
            "-I", INCLUDE, "-o", tmp, SRC_CALL]
     if verbose:
         print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("the compiler failed:\n" + res.stdout + res.stderr)
+    try:
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        failed = "" if res.returncode == 0 else "exit status %d\n" % res.returncode + res.stdout + res.stderr
+    except OSError as e:
+        failed = str(e)
+    if failed:
+        warnings.warn("the native caller _rc_call is not built; calls go through ctypes:\n" + failed)
+        return None
     os.replace(tmp, CALL_LIB)
     return CALL_LIB
 

@@ -1,7 +1,7 @@
 """Thin Python binding of ``librc_cohort.so`` (the C ABI in include/rc_cohort.h).
 
-Argument marshalling only (ctypes; a small native module for the calls made
-once per launch): every step of the transition runs in the HIP kernels.
+Argument marshalling only (ctypes; a small native module, where it is built,
+for the calls made once per launch): every step of the transition runs in the HIP kernels.
 There is no CPU fallback -- if the library is missing or no gfx950
 device is usable, the calls raise.
 
@@ -100,8 +100,9 @@ class RcError(RuntimeError):
 
 
 _lib: Optional[ctypes.CDLL] = None
-# Set with _lib: the native caller of the two chain entry points (see
-# csrc/rc_call.c) and their addresses.
+# The native caller of the two chain entry points (see csrc/rc_call.c) and
+# their addresses, set with _lib; None where it is not built or the library
+# lacks them: those calls go through ctypes.
 _call = None
 _fn_run_chain = _fn_run_chain_noalloc = None
 
@@ -149,14 +150,13 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.rc_cohort_plan_info.restype = ctypes.c_int
     try:
         from . import _rc_call
-    except ImportError as e:
-        raise RuntimeError("_rc_call.so is not built (run paper_2608_12123_amd/build.py or "
-                           "__graft_entry__.build())") from e
-    _call = _rc_call.call
+    except ImportError:
+        _rc_call = None
     _fn_run_chain = ctypes.cast(lib.rc_cohort_run_chain, ctypes.c_void_p).value
     if "rc_cohort_run_chain_noalloc" not in missing:
         _fn_run_chain_noalloc = ctypes.cast(lib.rc_cohort_run_chain_noalloc, ctypes.c_void_p).value
     _lib = lib
+    _call = _rc_call and _rc_call.call  # last: another thread calls through it at once
     return lib
 
 
@@ -253,8 +253,13 @@ def rc_cohort_run_chain(h, buffers: RcBuffers, step0: int, n_steps: int, mode: i
                         check: bool = True) -> int:
     if _call is None:
         load_library()
-    st = _call(_fn_run_chain, h, buffers, step0, n_steps, mode, cohort_begin, cohort_end,
-               _stream_handle(stream))
+    if _call is not None:
+        st = _call(_fn_run_chain, h, buffers, step0, n_steps, mode, cohort_begin, cohort_end,
+                   _stream_handle(stream))
+    else:
+        st = load_library().rc_cohort_run_chain(h, ctypes.byref(buffers), step0 & 0xFFFFFFFF,
+                                                n_steps, mode, cohort_begin, cohort_end,
+                                                _stream_handle(stream))
     if check and st != RC_OK:
         _check(st, "rc_cohort_run_chain")
     return st
@@ -267,8 +272,14 @@ def rc_cohort_run_chain_noalloc(h, buffers: RcBuffers, step0: int, n_steps: int,
     library's fixed device array (no device allocation by the call)."""
     if _call is None:
         load_library()
-    st = _call(_fn_run_chain_noalloc, h, buffers, step0, n_steps, mode, cohort_begin, cohort_end,
-               _stream_handle(stream))
+    if _call is not None and _fn_run_chain_noalloc:
+        st = _call(_fn_run_chain_noalloc, h, buffers, step0, n_steps, mode, cohort_begin,
+                   cohort_end, _stream_handle(stream))
+    else:
+        st = load_library().rc_cohort_run_chain_noalloc(h, ctypes.byref(buffers),
+                                                        step0 & 0xFFFFFFFF, n_steps, mode,
+                                                        cohort_begin, cohort_end,
+                                                        _stream_handle(stream))
     if check:
         _check(st, "rc_cohort_run_chain_noalloc")
     return st
