@@ -5,12 +5,15 @@
  * stream object made for each call, it cost the host 7.1 us.  call() passes
  * the same arguments to the same C entry point in about 0.3 us:
  *
+ *   bind(handle_type, buffers_type)
  *   call(fn, handle, buffers, a0, a1, a2, a3, a4, stream) -> status
  *
- * fn is the address of the entry point; handle a c_void_p, an address or
- * None; buffers an object with the bytes of an rc_buffers; a0..a4 integers,
- * taken modulo 2^32 as ctypes takes a c_uint32; stream an address or None.
- * The interpreter lock is released during the call.
+ * fn is the address of the entry point; handle a handle_type (ctypes'
+ * c_void_p), an address or None; buffers a buffers_type (the ctypes structure
+ * of an rc_buffers); a0..a4 integers, taken modulo 2^32 as ctypes takes a
+ * c_uint32; stream an address or None.  Any other form is a TypeError, and
+ * the binding hands it to ctypes, which converts or refuses it by its own
+ * rules.  The interpreter lock is released during the call.
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -21,7 +24,24 @@
 
 typedef int (*chain_fn)(rc_cohort *, const rc_buffers *, uint32_t, uint32_t, int, uint32_t, uint32_t, void *);
 
-/* An address from None, an integer or an object holding one pointer. */
+static PyTypeObject *handle_type, *buffers_type;
+
+static PyObject *bind(PyObject *self, PyObject *args)
+{
+    PyTypeObject *h, *b;
+    (void)self;
+    if (!PyArg_ParseTuple(args, "O!O!", &PyType_Type, &h, &PyType_Type, &b)) return NULL;
+    Py_INCREF(h);
+    Py_INCREF(b);
+    Py_XDECREF(handle_type);
+    Py_XDECREF(buffers_type);
+    handle_type = h;
+    buffers_type = b;
+    Py_RETURN_NONE;
+}
+
+/* An address from None, an integer (modulo the address size, as ctypes takes
+ * one) or a handle_type. */
 static int as_pointer(PyObject *o, void **out)
 {
     if (o == Py_None) {
@@ -29,8 +49,12 @@ static int as_pointer(PyObject *o, void **out)
         return 0;
     }
     if (PyLong_Check(o)) {
-        *out = PyLong_AsVoidPtr(o);
+        *out = (void *)(uintptr_t)PyLong_AsUnsignedLongLongMask(o);
         return PyErr_Occurred() ? -1 : 0;
+    }
+    if (!handle_type || !PyObject_TypeCheck(o, handle_type)) {
+        PyErr_SetString(PyExc_TypeError, "not a pointer");
+        return -1;
     }
     Py_buffer b;
     if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) return -1;
@@ -61,8 +85,12 @@ static PyObject *call(PyObject *self, PyObject *const *args, Py_ssize_t n)
         return NULL;
     }
     Py_buffer b; /* held during the call */
+    if (!buffers_type || !PyObject_TypeCheck(args[2], buffers_type)) {
+        PyErr_SetString(PyExc_TypeError, "buffers is not an RcBuffers");
+        return NULL;
+    }
     if (PyObject_GetBuffer(args[2], &b, PyBUF_SIMPLE) != 0) return NULL;
-    if (b.len != (Py_ssize_t)sizeof(rc_buffers)) {
+    if (b.len < (Py_ssize_t)sizeof(rc_buffers)) { /* a subclass may hold more */
         PyBuffer_Release(&b);
         PyErr_SetString(PyExc_TypeError, "buffers is not an RcBuffers");
         return NULL;
@@ -77,6 +105,7 @@ static PyObject *call(PyObject *self, PyObject *const *args, Py_ssize_t n)
 }
 
 static PyMethodDef methods[] = {
+    {"bind", bind, METH_VARARGS, "bind(handle_type, buffers_type): the types that call() takes"},
     {"call", (PyCFunction)(void (*)(void))call, METH_FASTCALL,
      "call(fn, handle, buffers, a0, a1, a2, a3, a4, stream): the status of a chain entry point"},
     {NULL, NULL, 0, NULL},

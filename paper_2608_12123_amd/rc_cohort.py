@@ -156,7 +156,9 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     if "rc_cohort_run_chain_noalloc" not in missing:
         _fn_run_chain_noalloc = ctypes.cast(lib.rc_cohort_run_chain_noalloc, ctypes.c_void_p).value
     _lib = lib
-    _call = _rc_call and _rc_call.call  # last: another thread calls through it at once
+    if _rc_call is not None:
+        _rc_call.bind(ctypes.c_void_p, RcBuffers)
+        _call = _rc_call.call  # last: another thread calls through it at once
     return lib
 
 
@@ -253,13 +255,17 @@ def rc_cohort_run_chain(h, buffers: RcBuffers, step0: int, n_steps: int, mode: i
                         check: bool = True) -> int:
     if _call is None:
         load_library()
+    stream = _stream_handle(stream)
+    st = None
     if _call is not None:
-        st = _call(_fn_run_chain, h, buffers, step0, n_steps, mode, cohort_begin, cohort_end,
-                   _stream_handle(stream))
-    else:
+        try:
+            st = _call(_fn_run_chain, h, buffers, step0, n_steps, mode, cohort_begin, cohort_end,
+                       stream)
+        except TypeError:
+            pass  # a form that ctypes takes, or refuses with its own error
+    if st is None:
         st = load_library().rc_cohort_run_chain(h, ctypes.byref(buffers), step0 & 0xFFFFFFFF,
-                                                n_steps, mode, cohort_begin, cohort_end,
-                                                _stream_handle(stream))
+                                                n_steps, mode, cohort_begin, cohort_end, stream)
     if check and st != RC_OK:
         _check(st, "rc_cohort_run_chain")
     return st
@@ -272,14 +278,18 @@ def rc_cohort_run_chain_noalloc(h, buffers: RcBuffers, step0: int, n_steps: int,
     library's fixed device array (no device allocation by the call)."""
     if _call is None:
         load_library()
+    stream = _stream_handle(stream)
+    st = None
     if _call is not None and _fn_run_chain_noalloc:
-        st = _call(_fn_run_chain_noalloc, h, buffers, step0, n_steps, mode, cohort_begin,
-                   cohort_end, _stream_handle(stream))
-    else:
+        try:
+            st = _call(_fn_run_chain_noalloc, h, buffers, step0, n_steps, mode, cohort_begin,
+                       cohort_end, stream)
+        except TypeError:
+            pass  # as in rc_cohort_run_chain
+    if st is None:
         st = load_library().rc_cohort_run_chain_noalloc(h, ctypes.byref(buffers),
                                                         step0 & 0xFFFFFFFF, n_steps, mode,
-                                                        cohort_begin, cohort_end,
-                                                        _stream_handle(stream))
+                                                        cohort_begin, cohort_end, stream)
     if check:
         _check(st, "rc_cohort_run_chain_noalloc")
     return st

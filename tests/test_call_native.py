@@ -52,3 +52,55 @@ def test_refused(call):
     assert rc.rc_cohort_run_chain(None, b, 0, 1, 0, 0, 1, stream=0, check=False) == rc.RC_E_INVALID
     with pytest.raises(rc.RcError):
         rc.rc_cohort_run_chain_noalloc(None, b, 0, 1, 0, 0, 1, stream=0)
+
+
+# Forms of an argument: whatever ctypes takes is taken with the same value,
+# whatever it refuses is refused with its error.
+FORMS = [
+    ("n_steps", ctypes.c_uint32(8)), ("n_steps", np.int64(8)), ("n_steps", True), ("n_steps", 8.0),
+    ("n_steps", "8"), ("n_steps", None), ("mode", ctypes.c_int(1)), ("mode", ctypes.c_uint32(1)),
+    ("step0", 1 << 35), ("step0", 2.0), ("cohort_end", ctypes.c_uint32(3)),
+    ("h", ctypes.c_uint64(0x1234)), ("h", np.array([0x1234], dtype=np.uint64)), ("h", bytearray(8)),
+    ("h", -1), ("h", 1 << 70), ("buffers", bytearray(56)), ("buffers", np.zeros(7, dtype=np.uint64)),
+    ("buffers", (ctypes.c_char * 56)()), ("buffers", None),
+]
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("name,value", FORMS, ids=lambda v: v if isinstance(v, str) else type(v).__name__)
+def test_forms_are_those_of_ctypes(call, monkeypatch, name, value, noalloc):
+    seen = []
+
+    @SIG
+    def fn(*a):
+        seen.append(a)
+        return 0
+
+    class Lib:  # the entry points as load_library declares them
+        pass
+    real = rc.load_library()
+    addr = ctypes.cast(fn, ctypes.c_void_p).value
+    proto = ctypes.CFUNCTYPE(ctypes.c_int)
+    for n in ("rc_cohort_run_chain", "rc_cohort_run_chain_noalloc"):
+        f = proto(addr)
+        f.argtypes, f.restype = getattr(real, n).argtypes, ctypes.c_int
+        setattr(Lib, n, staticmethod(f))
+    monkeypatch.setattr(rc, "_lib", Lib)
+    monkeypatch.setattr(rc, "_fn_run_chain", addr)
+    monkeypatch.setattr(rc, "_fn_run_chain_noalloc", addr)
+    buffers = rc.RcBuffers(1, 2, 3, 4, 5, 6, 77)
+    args = {"h": ctypes.c_void_p(0x4321), "buffers": buffers, "step0": 5, "n_steps": 16, "mode": 1,
+            "cohort_begin": 2, "cohort_end": 9, "stream": 0}
+    args[name] = value
+    run = rc.rc_cohort_run_chain_noalloc if noalloc else rc.rc_cohort_run_chain
+
+    def outcome(native):
+        monkeypatch.setattr(rc, "_call", call if native else None)
+        seen.clear()
+        try:
+            run(**args)
+        except Exception as e:
+            assert not seen
+            return type(e)
+        return list(seen)
+    assert outcome(True) == outcome(False)
