@@ -193,6 +193,16 @@ def _ptr(a: Optional[np.ndarray]):
 _torch_c = None  # torch's C module, once torch has initialised its device
 
 
+def _forget_torch_c():
+    global _torch_c
+    _torch_c = None
+
+
+# A forked child has no usable device: there the next call asks torch again,
+# which raises, instead of launching on its parent's stream.
+os.register_at_fork(after_in_child=_forget_torch_c)
+
+
 def _current_stream() -> int:
     """The raw handle of torch's current stream on its current device (no
     stream object is made: this runs once per launch)."""
