@@ -319,8 +319,12 @@ enum : uint32_t {
     TI_FIRST = 28    // bits 28..29: first wavefront in the workgroup
 };
 
+// Also clears the handle's `n_words` counter words (a memset is 8 us of the
+// host's time, this launch 3).
 __global__ __launch_bounds__(256) void rc_lanes_kernel(const uint32_t* wdesc, const uint32_t* offsets,
-                                                       uint32_t n_cohorts, uint32_t* lane_s, uint2* lane_i) {
+                                                       uint32_t n_cohorts, uint32_t* lane_s, uint2* lane_i,
+                                                       uint32_t* words, uint32_t n_words) {
+    if (blockIdx.x == 0u && threadIdx.x < n_words) words[threadIdx.x] = 0u;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = blockIdx.x * 4u + (threadIdx.x >> 6);
     const LaneCohort L = lane_cohort(wdesc + (size_t)wave * WD_WORDS, offsets, lane, 0u, n_cohorts);
@@ -1962,16 +1966,17 @@ struct rc_cohort {
     uint32_t chain_threads = 256;  // threads of a chain workgroup
     std::vector<uint32_t> offsets;  // host copy [C+1]
     Plan plan;
+    // All device memory of the handle is one allocation (see rc_cohort_create).
+    char* d_block = nullptr;
     uint32_t* d_offsets = nullptr;
     uint32_t* d_raw = nullptr;
     uint32_t* d_cdf = nullptr;
     uint32_t* d_img = nullptr;
-    uint32_t* d_span = nullptr;
     uint32_t* d_wdesc = nullptr;
     uint2* d_lane_i = nullptr;     // plan lanes (see rc_lanes_kernel)
-    uint32_t* d_lane_s = nullptr;  // in the same allocation
+    uint32_t* d_lane_s = nullptr;
     uint32_t table_wgs = 256;      // table image: workgroups that fit the device at once
-    uint32_t* d_where = nullptr;  // host round trip: [N] slot -> sid | d << 31
+    uint32_t* d_where = nullptr;  // host round trip: [N] session -> slot | d << 31
     uint32_t* d_ctr = nullptr;
     uint32_t* h_word = nullptr;  // pinned
     uint32_t parity = 0;
@@ -1993,15 +1998,7 @@ void free_handle(rc_cohort* h) {
     if (!h) return;
     if (h->device >= 0) {
         DeviceGuard g(h->device);
-        (void)hipFree(h->d_offsets);
-        (void)hipFree(h->d_raw);
-        (void)hipFree(h->d_cdf);
-        (void)hipFree(h->d_img);
-        (void)hipFree(h->d_span);
-        (void)hipFree(h->d_wdesc);
-        (void)hipFree(h->d_lane_i);
-        (void)hipFree(h->d_where);
-        (void)hipFree(h->d_ctr);
+        (void)hipFree(h->d_block);
         if (h->h_word) (void)hipHostFree(h->h_word);
         if (h->hrt_done) (void)hipEventDestroy(h->hrt_done);
     }
@@ -2037,11 +2034,8 @@ int noalloc_init(int dev) {
     return RC_OK;
 }
 
-template <typename T>
-int dev_upload(T** dst, const void* src, size_t bytes) {
-    if (hipMalloc((void**)dst, bytes < 16 ? 16 : bytes) != hipSuccess) return RC_E_NOMEM;
-    if (bytes && hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice) != hipSuccess) return RC_E_DEVICE;
-    return RC_OK;
+int dev_upload(uint32_t* dst, const uint32_t* src, size_t words) {
+    return !words || hipMemcpy(dst, src, words * 4u, hipMemcpyHostToDevice) == hipSuccess ? RC_OK : RC_E_DEVICE;
 }
 
 // Is [p, p + bytes) inside one HIP allocation of device `dev`?
@@ -2409,28 +2403,52 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
     h->offsets.assign(desc->cohort_offsets, desc->cohort_offsets + h->C + 1u);
     build_plan(h->offsets.data(), h->C, h->nwave, h->plan);
 
-    int rc = RC_OK;
-    if (rc == RC_OK) rc = dev_upload(&h->d_offsets, h->offsets.data(), h->offsets.size() * 4u);
-    if (rc == RC_OK) rc = dev_upload(&h->d_raw, desc->table, (size_t)R * 16u * 4u);
-    if (rc == RC_OK) rc = dev_upload(&h->d_cdf, desc->route_cdf, (size_t)h->ra.cdf_n * 4u);
-    if (rc == RC_OK && hipMalloc((void**)&h->d_img, (size_t)h->img_words * 4u) != hipSuccess) rc = RC_E_NOMEM;
-    if (rc == RC_OK && hipMalloc((void**)&h->d_span, 16) != hipSuccess) rc = RC_E_NOMEM;
-    if (rc == RC_OK && hipMemset(h->d_span, 0, 16) != hipSuccess) rc = RC_E_DEVICE;
-    if (rc == RC_OK) rc = dev_upload(&h->d_wdesc, h->plan.wdesc.data(), h->plan.wdesc.size() * 4u);
-    if (rc == RC_OK && hipMalloc((void**)&h->d_where, (size_t)h->N * sizeof(uint32_t)) != hipSuccess) rc = RC_E_NOMEM;
-    if (rc == RC_OK && hipMalloc((void**)&h->d_ctr, 2 * sizeof(uint32_t)) != hipSuccess) rc = RC_E_NOMEM;
-    if (rc == RC_OK && hipMemset(h->d_ctr, 0, 2 * sizeof(uint32_t)) != hipSuccess) rc = RC_E_DEVICE;
+    // One device allocation for everything the handle holds, in parts that
+    // start at multiples of 256 bytes.  An allocation and its release cost the
+    // host little where they are small, but about 40 us together from a few
+    // MiB up, and the release after a create that also cleared words with two
+    // memsets waited 20 to 40 us: create and destroy of 1,000 sessions took
+    // 92 + 75 us with an allocation for each array and two memsets, 77 + 28 us
+    // so; of a million sessions 276 + 116 us, 260 + 41 us.
+    size_t block_bytes = 0;
+    auto part = [&](size_t bytes) {
+        const size_t at = block_bytes;
+        block_bytes += (bytes + 255u) & ~(size_t)255u;
+        return at;
+    };
+    const size_t lanes = (size_t)h->plan.n_bins * na;
+    const size_t at_lane_i = part(lanes * sizeof(uint2));
+    const size_t at_lane_s = part(lanes * 4u);
+    const size_t at_where = part((size_t)h->N * 4u);
+    const size_t at_wdesc = part(h->plan.wdesc.size() * 4u);
+    const size_t at_offsets = part(h->offsets.size() * 4u);
+    const size_t at_raw = part((size_t)R * 16u * 4u);
+    const size_t at_cdf = part((size_t)h->ra.cdf_n * 4u);
+    const size_t at_img = part((size_t)h->img_words * 4u);
+    const size_t at_words = part(3u * 4u);  // two counters, then the largest guide bucket span
+    int rc = hipMalloc((void**)&h->d_block, block_bytes) == hipSuccess ? RC_OK : RC_E_NOMEM;
+    if (rc == RC_OK) {
+        auto words_at = [&](size_t at) { return reinterpret_cast<uint32_t*>(h->d_block + at); };
+        h->d_lane_i = reinterpret_cast<uint2*>(h->d_block + at_lane_i);
+        h->d_lane_s = words_at(at_lane_s);
+        h->d_where = words_at(at_where);
+        h->d_wdesc = words_at(at_wdesc);
+        h->d_offsets = words_at(at_offsets);
+        h->d_raw = words_at(at_raw);
+        h->d_cdf = words_at(at_cdf);
+        h->d_img = words_at(at_img);
+        h->d_ctr = words_at(at_words);
+    }
+    if (rc == RC_OK) rc = dev_upload(h->d_offsets, h->offsets.data(), h->offsets.size());
+    if (rc == RC_OK) rc = dev_upload(h->d_raw, desc->table, (size_t)R * 16u);
+    if (rc == RC_OK) rc = dev_upload(h->d_cdf, desc->route_cdf, h->ra.cdf_n);
+    if (rc == RC_OK) rc = dev_upload(h->d_wdesc, h->plan.wdesc.data(), h->plan.wdesc.size());
     if (rc == RC_OK && hipHostMalloc((void**)&h->h_word, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) rc = RC_E_NOMEM;
     if (rc == RC_OK && hipEventCreateWithFlags(&h->hrt_done, hipEventDisableTiming) != hipSuccess) rc = RC_E_DEVICE;
     if (rc == RC_OK) rc = noalloc_init(hip_device);
-    // plan lanes: 8 bytes each, then 4 bytes each
-    const size_t lanes = (size_t)h->plan.n_bins * na;
-    if (rc == RC_OK && hipMalloc((void**)&h->d_lane_i, lanes * (sizeof(uint2) + sizeof(uint32_t))) != hipSuccess)
-        rc = RC_E_NOMEM;
     if (rc == RC_OK) {
-        h->d_lane_s = reinterpret_cast<uint32_t*>(h->d_lane_i + lanes);
         hipLaunchKernelGGL(rc_lanes_kernel, dim3(h->plan.n_bins), dim3(na), 0, 0, h->d_wdesc, h->d_offsets, h->C,
-                           h->d_lane_s, h->d_lane_i);
+                           h->d_lane_s, h->d_lane_i, h->d_ctr, 3u);
         rc = launch_ok();
     }
     if (rc == RC_OK) {
@@ -2438,7 +2456,7 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
         ia.raw = h->d_raw;
         ia.cdf = h->d_cdf;
         ia.img = h->d_img;
-        ia.max_span = h->d_span;
+        ia.max_span = h->d_ctr + 2;
         ia.n_routes = R;
         ia.row_words = row_words;
         ia.full = h->full ? 1u : 0u;
@@ -2455,7 +2473,7 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
         hipLaunchKernelGGL(rc_prep_kernel, dim3((h->img_words + 255u) / 256u), dim3(256), 0, 0, ia);
         uint32_t span = 0;
         // the copy waits for both kernels: callers' streams need not
-        if (launch_ok() != RC_OK || hipMemcpy(&span, h->d_span, 4, hipMemcpyDeviceToHost) != hipSuccess)
+        if (launch_ok() != RC_OK || hipMemcpy(&span, h->d_ctr + 2, 4, hipMemcpyDeviceToHost) != hipSuccess)
             rc = RC_E_DEVICE;
         h->ra.guide_top = 0;
         while (span && (h->ra.guide_top << 1) <= span) h->ra.guide_top = h->ra.guide_top ? h->ra.guide_top << 1 : 1u;
