@@ -364,14 +364,10 @@ __device__ __forceinline__ LaneCohort lane_record(const uint32_t* __restrict__ l
     return L;
 }
 
-// The same from the wavefront's descriptor where one cohort has the whole
-// wavefront (a scalar load, the shorter latency: one 256-session cohort, T =
-// 7, 4.31 us against 4.47 from the record), else from the record.
-template <bool MULTI>
-__device__ __forceinline__ LaneCohort lane_view(const uint32_t* __restrict__ wd, const uint32_t* __restrict__ lane_s,
-                                                const uint2* __restrict__ lane_i, size_t at, uint32_t lane,
-                                                uint32_t s_lo, uint32_t s_n) {
-    if (!MULTI && uni(wd[WD_NCOH]) > 1u) return lane_record(lane_s, lane_i, at, s_lo, s_n);
+// The same from the wavefront's descriptor, for a wavefront of a cohort of
+// more than 64 sessions: one scalar load.
+__device__ __forceinline__ LaneCohort lane_descriptor(const uint32_t* __restrict__ wd, uint32_t lane, uint32_t s_lo,
+                                                      uint32_t s_n) {
     LaneCohort L;
     L.s = uni(wd[WD_S0]) + lane;
     L.c = uni(wd[WD_CFIRST]);
@@ -379,8 +375,7 @@ __device__ __forceinline__ LaneCohort lane_view(const uint32_t* __restrict__ wd,
     L.k = uni(wd[WD_KFIRST]);
     L.flags = uni(wd[WD_FLAGS]);
     L.active = lane < uni(wd[WD_NACT]) && L.s - s_lo < s_n;
-    // a sub-wavefront cohort's lanes start at lane 0
-    L.seg = MULTI ? 0ull : L.k >= 64u ? ~0ull : ((1ull << L.k) - 1ull);
+    L.seg = 0ull;
     return L;
 }
 
@@ -620,13 +615,18 @@ struct ChainF {
 
         const uint32_t rows_b = a.rows_off * 4u;  // byte offset of the mask rows in LDS
         LaneCohort L;
-        // One lane per session at W <= 8 keeps little else in flight while it
-        // waits, and takes the record throughout: 200,000 sessions in ragged
-        // cohorts, W = 8, T = 4, 12.9 us with lane_view, 10.8 without; at W =
-        // 16, T = 4, 300,000 sessions in 256-session cohorts 15.0 and 15.5.
-        if constexpr (SPLIT || (MULTI && WMAX >= 16))
-            L = lane_view<MULTI>(a.wdesc + ((size_t)bin * NWAVE + wa) * WD_WORDS, a.lane_s, a.lane_i,
-                          (size_t)bin * NLA + alane, lane, a.s_lo, a.s_n);
+        // Cohorts of more than 64 sessions, from W = 9: the descriptor, which
+        // spares the traffic of the records (12 bytes a session): 500,000
+        // sessions in 256-session cohorts, W = 16, T = 1, 14.9 us against
+        // 16.0 with the records; W = 32, T = 4, 30.0 and 31.2.  At W <= 8 the
+        // records are no slower: W = 8, 130-session cohorts, within 1%.
+        // Sub-wavefront bins: the records.  Looking first whether one cohort
+        // has the whole wavefront, and then taking its descriptor, costs more
+        // than the records: 100,000 sessions, W = 32, R = 256 CDF, T = 1, 6.7
+        // us against 6.3 with 64-session cohorts and 6.7 against 6.4 with
+        // 32-session ones.
+        if constexpr (MULTI && WMAX >= 16)
+            L = lane_descriptor(a.wdesc + ((size_t)bin * NWAVE + wa) * WD_WORDS, lane, a.s_lo, a.s_n);
         else
             L = lane_record(a.lane_s, a.lane_i, (size_t)bin * NLA + alane, a.s_lo, a.s_n);
         const uint32_t soff = L.s << 2;
