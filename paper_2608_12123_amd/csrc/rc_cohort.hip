@@ -1645,7 +1645,7 @@ __global__ __launch_bounds__(1024, 4) void rc_table_kernel(TableArgs a) {
 // partition of its cohort), and adds the workgroup's taken count to
 // ctr[parity] (the 4-byte word the host reads).  Block 0 clears the other
 // parity's counter for the next step.  A workgroup takes up to four bins at
-// a time, and there are at most DECIDE_WGS (see the launch): the adds to the one word are
+// a time, and there are at most DECIDE_WGS (see decide_few): the adds to the one word are
 // performed one after the other, about 11 ns each (a workgroup and an add per
 // bin: 391 bins spent 4.3 us of 6.5 on them).
 struct DecideArgs {
@@ -1660,8 +1660,6 @@ struct DecideArgs {
     uint32_t s_n;             // stepped sessions, from where_lo
     uint32_t bins_a_lo, bins_a_n, bins_b_lo, n_units, parity, where_lo;
 };
-
-constexpr uint32_t DECIDE_WGS = 256;
 
 __global__ __launch_bounds__(1024) void rc_decide_kernel(DecideArgs a) {
     __shared__ uint32_t cnt[2][16 + 4];  // taken counts of the wavefronts (a cohort reads four from its first)
@@ -2213,13 +2211,9 @@ int run_host_roundtrip(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32
     uint32_t a_lo, a_n, b_lo, b_n;
     bins_of_range(h->plan, cb, ce, a_lo, a_n, b_lo, b_n);
     const uint32_t units = a_n + b_n;
-    // Few workgroups, for their adds to the one counter -- unless hardly any
-    // bin has a taken session (under one in four), so that hardly any adds:
-    // then a workgroup per bin.  100,000 sessions, 391 bins, 8 steps: 202 /
-    // 190 / 183 us with 1 / 2 / 4 bins at p = 0.5, 163 / 168 / 171 us at p = 0.
-    const bool adds = h->thr >= 64u;
-    const uint32_t per = !adds ? 1u : units < 4u ? units : 4u, wgs = (units + per - 1u) / per;
-    const uint32_t grid = adds && wgs > DECIDE_WGS ? DECIDE_WGS : wgs;
+    const bool few = decide_few(units, h->thr);
+    const uint32_t per = !few ? 1u : units < 4u ? units : 4u, wgs = (units + per - 1u) / per;
+    const uint32_t grid = few && wgs > DECIDE_WGS ? DECIDE_WGS : wgs;
     const uint32_t lo = h->offsets[cb], hi = h->offsets[ce];
     const uint32_t n_range = hi - lo;
     const uint32_t body_grid = (n_range + 255u) / 256u;

@@ -56,6 +56,21 @@ void build_plan(const uint32_t* off, uint32_t C, uint32_t nw_per_bin, Plan& P);
 void bins_of_range(const Plan& P, uint32_t cb, uint32_t ce, uint32_t& a_lo, uint32_t& a_n,
                    uint32_t& b_lo, uint32_t& b_n);
 
+// The decide kernel of the host round trip: whether it takes few workgroups
+// (at most DECIDE_WGS, up to four bins at a time) or one per bin.  A bin's
+// workgroup adds to the one counter if it has a taken session, and the adds
+// are performed one after the other, about 11 ns each; few workgroups cost
+// about 0.7 us a step where hardly any adds.  So: few, unless under one bin in
+// four adds (256 sessions, thr of 65,536 taken: thr / 256 of the bins, a
+// little less in truth) and under DECIDE_WGS of them do.  391 bins, 8 steps:
+// 202 / 190 / 183 us with 1 / 2 / 4 bins at a time at thr = 32768, 153 / 157
+// with one and few at 63, 145 / 151 at 0.  3,907 bins, 8 steps of W = 4, one
+// and few: 313 / 274 at 63, 258 / 267 at 16, 250 / 255 at 0.
+constexpr uint32_t DECIDE_WGS = 256;
+inline bool decide_few(uint32_t units, uint32_t thr) {
+    return thr >= 64u || (uint64_t)units * thr / 256u > DECIDE_WGS;
+}
+
 }  // namespace rc_plan
 
 #endif  // RC_PLAN_H
