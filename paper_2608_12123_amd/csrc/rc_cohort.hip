@@ -2394,8 +2394,13 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
     h->chain_threads = (split ? 2u : 1u) * na;
     h->chain_lds_bytes = lds_image + lds_after_image;
 
-    h->offsets.assign(desc->cohort_offsets, desc->cohort_offsets + h->C + 1u);
-    build_plan(h->offsets.data(), h->C, h->nwave, h->plan);
+    try {
+        h->offsets.assign(desc->cohort_offsets, desc->cohort_offsets + h->C + 1u);
+        build_plan(h->offsets.data(), h->C, h->nwave, h->plan);
+    } catch (const std::bad_alloc&) {
+        free_handle(h);
+        return RC_E_NOMEM;
+    }
 
     // One device allocation for everything the handle holds, in parts that
     // start at multiples of 256 bytes.  An allocation and its release cost the

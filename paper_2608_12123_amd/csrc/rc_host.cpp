@@ -6,6 +6,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <new>
 #include <vector>
 
 #include "rc_plan.h"
@@ -217,7 +218,11 @@ int rc_plan_lanes(const rc_cohort_desc* desc, uint32_t lanes_per_workgroup, uint
     if (v != RC_OK) return v;
     if (lanes_per_workgroup != 256u && lanes_per_workgroup != 512u) return RC_E_INVALID;
     Plan P;
-    build_plan(desc->cohort_offsets, desc->n_cohorts, lanes_per_workgroup / 64u, P);
+    try {
+        build_plan(desc->cohort_offsets, desc->n_cohorts, lanes_per_workgroup / 64u, P);
+    } catch (const std::bad_alloc&) {
+        return RC_E_NOMEM;
+    }
     const uint32_t total = P.n_bins * lanes_per_workgroup;
     *n_lanes = total;
     if (!lane_session || !lane_cohort_out) return RC_OK;
