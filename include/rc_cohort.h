@@ -152,7 +152,7 @@ int rc_cohort_step(rc_cohort *h, const rc_buffers *b, uint32_t step,
  * RC_MODE_RESIDENT enqueues one kernel launch and returns without waiting.
  * RC_MODE_HOST_ROUNDTRIP synchronizes the stream once per step (that
  * observation is the mechanism being measured) and returns after enqueuing
- * the last body kernel.  Its per-step scratch (a slot permutation and two
+ * the last body kernel.  Its per-step scratch (the sessions' slots and two
  * counter words) belongs to the handle; a host-round-trip call first makes
  * its stream wait for the previous host-round-trip call on the same handle
  * (an event the handle records after that call's last body kernel), so
@@ -206,7 +206,7 @@ int rc_cohort_run_floor(rc_cohort *h, const rc_buffers *b, const uint32_t *decis
  * captured into a HIP graph, tight serving loops, harnesses that forbid
  * hipMalloc.  Exactly rc_cohort_run_chain (same arguments, same outputs),
  * except that in RC_MODE_HOST_ROUNDTRIP the per-step scratch -- the
- * permutation of the stepped sessions and the two counter words -- lives in
+ * slots of the stepped sessions and the two counter words -- lives in
  * one fixed array of device memory of the library (4 MiB plus 256 bytes per
  * device, held until the process ends) instead of the handle's buffers, and
  * the counter words are cleared by a kernel launch (no memset) at the start
@@ -234,9 +234,10 @@ const char *rc_status_string(int status);
 /*
  * Kernel launches and device-to-host copies enqueued by the last successful
  * rc_cohort_run_chain / rc_cohort_step / rc_cohort_run_floor on this handle
- * (resident and floor: 1 and 0; host round trip: at least T + 1 launches
- * and exactly T copies).  Either output pointer may be NULL.  RC_E_INVALID
- * when h is NULL.
+ * (resident and floor: 1 and 0; host round trip: 2 T launches -- decide and
+ * body of every step -- and T copies, and one launch more, the counters'
+ * clear, through rc_cohort_run_chain_noalloc).  Either output pointer may be
+ * NULL.  RC_E_INVALID when h is NULL.
  */
 int rc_cohort_last_counts(const rc_cohort *h, uint32_t *launches, uint32_t *d2h_copies);
 
@@ -251,8 +252,8 @@ int rc_cohort_plan_info(const rc_cohort *h, uint32_t *n_workgroups,
 
 /*
  * Host-only inspection of the launch plan the library would build for
- * `desc` with workgroups of `lanes_per_workgroup` lanes (256 or 512; the
- * library picks one of these per handle).  No device is used.  Writes
+ * `desc` with workgroups of `lanes_per_workgroup` lanes (256, as the library
+ * launches it, or 512).  No device is used.  Writes
  * *n_lanes = bins * lanes_per_workgroup.  When both arrays are non-NULL
  * (capacity >= *n_lanes entries each, host memory) it also writes, for every
  * plan lane, the session it processes and that session's cohort, derived

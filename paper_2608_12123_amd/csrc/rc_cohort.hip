@@ -13,8 +13,10 @@
 //                     leave the chip.
 //   rc_decide_kernel  host-round-trip step, part 1 (Section 7 "Host round
 //                     trip"): decide + compact, publish a 4-byte word.
-//   rc_body_kernel    host-round-trip step, part 2: one route body over the
-//                     compacted list the host selected.
+//   rc_body_kernel    host-round-trip step, part 2: the route body the host
+//                     selected, or both in one launch, over the stepped
+//                     sessions in order; effects at the slots that part 1
+//                     left for them.
 //
 // Data layout (HBM, structure of arrays, leading dimension ld): state
 // [W][ld], outcome [ld], effects [T][ld] for sid and tool, [T][ld][4] for the
@@ -199,7 +201,10 @@ struct RouteArgs {
 // o mod R by the reciprocal m = floor(2^32 / R): o m / 2^32 is below o / R by
 // less than o / 2^32 < 1, so its floor is the quotient or one less, and one
 // conditional subtraction finishes it (a general 32-bit remainder is about
-// four times the instructions, on the serial path of the chain).
+// four times the instructions, on the serial path of the chain).  R = 23, us
+// per launch with the remainder and with this: 100,000 sessions, W = 32, T =
+// 16, 13.96 and 13.65; one 256-session cohort, W = 16, T = 32, 10.46 and
+// 10.15; a million sessions, bound by HBM, the same.
 __device__ __forceinline__ uint32_t mod_routes(uint32_t o, const RouteArgs& ra) {
     const uint32_t x = o - __umulhi(o, ra.mod_recip) * ra.n_routes;  // < 2 R
     const uint32_t y = x - ra.n_routes;
@@ -238,7 +243,11 @@ __device__ __forceinline__ uint32_t route_of(uint32_t o, const RouteArgs& ra,
         // At most three thresholds are left (one, where no bucket holds more):
         // read together, one LDS latency, and counted.  Those past the answer
         // are above o; the padding behind the last one counts only for
-        // o = 2^32 - 1, whose route is R - 1.
+        // o = 2^32 - 1, whose route is R - 1.  Against a search to the end,
+        // us per launch: routes of Zipf(3) over 23, one 256-session cohort, W
+        // = 16, T = 32, 15.58 and 14.39; over 1,000, 100,000 sessions, W = 64,
+        // T = 16, 35.17 and 34.08.  Even or Zipf(1.1) routes, at most one
+        // threshold a bucket or few: within 1.5% either way.
         uint32_t below = cdf[pos] <= o;
         if (ra.guide_top > 1u) {
             const uint32_t v1 = cdf[pos + 1u], v2 = cdf[pos + 2u];
@@ -261,8 +270,7 @@ struct LaneCohort {
 };
 
 __device__ __forceinline__ LaneCohort lane_cohort(const uint32_t* __restrict__ wd,
-                                                  const uint32_t* __restrict__ offsets,
-                                                  uint32_t lane, uint32_t cb, uint32_t ce) {
+                                                  const uint32_t* __restrict__ offsets, uint32_t lane) {
     LaneCohort L;
     const uint32_t s0 = uni(wd[WD_S0]);
     const uint32_t n_act = uni(wd[WD_NACT]);
@@ -293,7 +301,7 @@ __device__ __forceinline__ LaneCohort lane_cohort(const uint32_t* __restrict__ w
     }
     L.b = b;
     L.k = k;
-    L.active = lane < n_act && L.c >= cb && L.c < ce;
+    L.active = lane < n_act;
     L.seg = 0;
     if (!(L.flags & WF_MULTI)) {
         uint32_t hi = lo + k;
@@ -322,12 +330,12 @@ enum : uint32_t {
 // Also clears the handle's `n_words` counter words (a memset is 8 us of the
 // host's time, this launch 3).
 __global__ __launch_bounds__(256) void rc_lanes_kernel(const uint32_t* wdesc, const uint32_t* offsets,
-                                                       uint32_t n_cohorts, uint32_t* lane_s, uint2* lane_i,
-                                                       uint32_t* words, uint32_t n_words) {
+                                                       uint32_t* lane_s, uint2* lane_i, uint32_t* words,
+                                                       uint32_t n_words) {
     if (blockIdx.x == 0u && threadIdx.x < n_words) words[threadIdx.x] = 0u;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = blockIdx.x * 4u + (threadIdx.x >> 6);
-    const LaneCohort L = lane_cohort(wdesc + (size_t)wave * WD_WORDS, offsets, lane, 0u, n_cohorts);
+    const LaneCohort L = lane_cohort(wdesc + (size_t)wave * WD_WORDS, offsets, lane);
     uint32_t v = 0u;
     if (L.flags & WF_MULTI)
         v = (1u << TI_MULTI) | (((L.flags >> 8) & 3u) << TI_WI) | ((((L.flags >> 16) - 1u) & 3u) << TI_NW) |
@@ -1242,6 +1250,15 @@ struct TableArgs {
 // place of the barriers 215 us (a wavefront's partly filled lines then meet
 // their neighbours' later), single wavefronts walking bins on their own with
 // one lane per session 232 us.
+//
+// Where it is slower than the form it replaces: one or two steps that stream
+// from HBM (from about 300,000 sessions) in partly filled wavefronts, whose
+// bins hold few sessions each.  A million sessions, T = 1, before and after:
+// 33-session cohorts, W = 49, 77 -> 105; 130-session cohorts, W = 64, 99 ->
+// 115; full wavefronts, W = 64, 84 -> 86.  It moves the same bytes there.
+// Words fetched two units ahead made those launches 20% slower still, bins in
+// XCD-contiguous order won 4% on them and lost 2% on full wavefronts, and one
+// lane per session in 1,024-lane persistent workgroups was slower than both.
 template <int NB, int RK, bool FLOOR>
 struct ChainT {
     static constexpr int TC = 4;
@@ -1656,7 +1673,7 @@ struct DecideArgs {
     uint32_t* ctr;            // [2]
     const uint32_t* lane_s;   // [bins][256] (see rc_lanes_kernel)
     const uint2* lane_i;
-    uint32_t thr, step, t_index, n_cohorts, n_sessions;
+    uint32_t thr, step, t_index, n_cohorts;
     uint32_t s_n;             // stepped sessions, from where_lo
     uint32_t bins_a_lo, bins_a_n, bins_b_lo, n_units, parity, where_lo;
 };
@@ -2185,8 +2202,8 @@ int run_resident(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32_t T,
 }
 
 // Where a host-round-trip call keeps its per-step scratch: the slot of
-// every stepped session (session s at where[s - lo]) and the two counter words of the 4-byte observation, plus
-// the event that orders the calls sharing them.
+// every stepped session (session s at where[s - lo]), the two counter words of
+// the 4-byte observation, and the event that orders the calls sharing them.
 struct HrtScratch {
     uint32_t* where;
     uint32_t* ctr;
@@ -2231,7 +2248,6 @@ int run_host_roundtrip(rc_cohort* h, const rc_buffers* b, uint32_t step0, uint32
         d.step = step0 + t;
         d.t_index = t;
         d.n_cohorts = h->C;
-        d.n_sessions = h->N;
         d.s_n = n_range;
         d.bins_a_lo = a_lo;
         d.bins_a_n = a_n;
@@ -2446,7 +2462,7 @@ int rc_cohort_create(const rc_cohort_desc* desc, int hip_device, rc_cohort** out
     if (rc == RC_OK && hipEventCreateWithFlags(&h->hrt_done, hipEventDisableTiming) != hipSuccess) rc = RC_E_DEVICE;
     if (rc == RC_OK) rc = noalloc_init(hip_device);
     if (rc == RC_OK) {
-        hipLaunchKernelGGL(rc_lanes_kernel, dim3(h->plan.n_bins), dim3(na), 0, 0, h->d_wdesc, h->d_offsets, h->C,
+        hipLaunchKernelGGL(rc_lanes_kernel, dim3(h->plan.n_bins), dim3(na), 0, 0, h->d_wdesc, h->d_offsets,
                            h->d_lane_s, h->d_lane_i, h->d_ctr, 3u);
         rc = launch_ok();
     }

@@ -156,17 +156,8 @@ void build_plan(const uint32_t* off, uint32_t C, uint32_t nw_per_bin, Plan& P) {
         P.last_b[c] = small ? (c ? P.last_b[c - 1] : -1) : (int32_t)c;
     }
 
-    // mark workgroups that contain a multi-wavefront cohort; count idle lanes
     uint32_t idle = 0;
-    for (uint32_t bb = 0; bb < P.n_bins; ++bb) {
-        bool any = false;
-        for (uint32_t w = 0; w < NW; ++w) any |= (P.wdesc[((size_t)bb * NW + w) * WD_WORDS + WD_FLAGS] & WF_MULTI) != 0u;
-        for (uint32_t w = 0; w < NW; ++w) {
-            uint32_t* d = &P.wdesc[((size_t)bb * NW + w) * WD_WORDS];
-            if (any) d[WD_FLAGS] |= WF_WGMULTI;
-            idle += 64u - d[WD_NACT];
-        }
-    }
+    for (size_t w = 0; w < (size_t)P.n_bins * NW; ++w) idle += 64u - P.wdesc[w * WD_WORDS + WD_NACT];
     P.idle_lanes = idle;
 }
 

@@ -28,7 +28,6 @@ enum : uint32_t {
 };
 enum : uint32_t {
     WF_MULTI = 1u,    // this wavefront is part of a cohort of > 64 sessions
-    WF_WGMULTI = 2u,  // some wavefront of the workgroup is (uniform per WG)
     // bits 8..15: index of this wavefront inside its cohort
     // bits 16..23: wavefronts of the cohort (at most 4)
     // bits 24..31: first wavefront (inside the workgroup) of the cohort

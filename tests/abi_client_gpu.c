@@ -220,7 +220,8 @@ static void run_shape(const Shape *s) {
         if (run == RUN_ALL || run == RUN_NOALLOC_RES)
             check(launches == 1u && copies == 0u, run_name[run], "one launch and no copy");
         if (run == RUN_HRT || run == RUN_NOALLOC_HRT)
-            check(launches >= T + 1u && copies == T, run_name[run], "T copies and at least T + 1 launches");
+            check(launches == 2u * T + (run == RUN_NOALLOC_HRT ? 1u : 0u) && copies == T, run_name[run],
+                  "T copies and 2 T launches, one more without allocation");
         check(hipMemcpy(got.state, b.state, in.n_state * 4u, hipMemcpyDeviceToHost) == hipSuccess &&
                   hipMemcpy(got.outcome, b.outcome, in.n_outcome * 4u, hipMemcpyDeviceToHost) == hipSuccess &&
                   hipMemcpy(got.sid, b.eff_sid, in.n_eff * 4u, hipMemcpyDeviceToHost) == hipSuccess &&

@@ -79,7 +79,7 @@ def test_noalloc_counts(orc):
     try:
         co.run_chain_noalloc(0, 3, rc.RC_MODE_HOST_ROUNDTRIP)
         launches, copies = co.last_counts()
-        assert copies == 3 and launches >= 3 + 1 + 1  # decides, bodies, the counter clear
+        assert copies == 3 and launches == 3 + 3 + 1  # decides, bodies, the counter clear
         co.run_chain_noalloc(0, 3, rc.RC_MODE_RESIDENT)
         assert co.last_counts() == (1, 0)
     finally:
