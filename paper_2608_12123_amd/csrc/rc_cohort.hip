@@ -387,6 +387,17 @@ __device__ __forceinline__ LaneCohort lane_descriptor(const uint32_t* __restrict
     return L;
 }
 
+// A sub-wavefront bin's: the descriptor where one cohort has the whole
+// wavefront, else the record.
+__device__ __forceinline__ LaneCohort lane_view(const uint32_t* __restrict__ wd, const uint32_t* __restrict__ lane_s,
+                                                const uint2* __restrict__ lane_i, size_t at, uint32_t lane,
+                                                uint32_t s_lo, uint32_t s_n) {
+    if (uni(wd[WD_NCOH]) > 1u) return lane_record(lane_s, lane_i, at, s_lo, s_n);
+    LaneCohort L = lane_descriptor(wd, lane, s_lo, s_n);
+    L.seg = L.k >= 64u ? ~0ull : ((1ull << L.k) - 1ull);  // the cohort starts at lane 0
+    return L;
+}
+
 // ---------------------------------------------------------------------------
 // Table image (built once per handle)
 // ---------------------------------------------------------------------------
@@ -628,12 +639,22 @@ struct ChainF {
         // sessions in 256-session cohorts, W = 16, T = 1, 14.9 us against
         // 16.0 with the records; W = 32, T = 4, 30.0 and 31.2.  At W <= 8 the
         // records are no slower: W = 8, 130-session cohorts, within 1%.
-        // Sub-wavefront bins: the records.  Looking first whether one cohort
-        // has the whole wavefront, and then taking its descriptor, costs more
-        // than the records: 100,000 sessions, W = 32, R = 256 CDF, T = 1, 6.7
-        // us against 6.3 with 64-session cohorts and 6.7 against 6.4 with
-        // 32-session ones.
-        if constexpr (MULTI && WMAX >= 16)
+        // Sub-wavefront bins: the records, but in the two-role split the
+        // descriptor of a wavefront that one cohort has to itself.  What that
+        // look costs the pipelined split: 100,000 sessions, W = 32, R = 256
+        // CDF, T = 1, 6.7 us against 6.3 with 64-session cohorts and 6.7
+        // against 6.4 with 32-session ones.  In the two-role split at W = 64
+        // it wins up to 4% where such wavefronts stream from HBM and loses 2
+        // to 6% where a wavefront has many cohorts (500,000 sessions, R = 200,
+        // T = 4: 53.6 us against 56.0 with 64-session cohorts, 307 against 299
+        // with one-session ones).  At W = 32 without it the compiler places
+        // the blocks of the kernel's other half otherwise: 391 cohorts of 256
+        // sessions, mod 256, T = 16, take 14.27 us against 14.07, their
+        // no-decision floor 14.92 against 14.52.
+        if constexpr (!MULTI && SPLIT && !PIPE)
+            L = lane_view(a.wdesc + ((size_t)bin * NWAVE + wa) * WD_WORDS, a.lane_s, a.lane_i, (size_t)bin * NLA + alane,
+                          lane, a.s_lo, a.s_n);
+        else if constexpr (MULTI && WMAX >= 16)
             L = lane_descriptor(a.wdesc + ((size_t)bin * NWAVE + wa) * WD_WORDS, lane, a.s_lo, a.s_n);
         else
             L = lane_record(a.lane_s, a.lane_i, (size_t)bin * NLA + alane, a.s_lo, a.s_n);
